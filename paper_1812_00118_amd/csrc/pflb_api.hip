@@ -189,9 +189,15 @@ int device_cus() {
     return n;
 }
 
-int pick_bz(const Geom& G, int lattice, int nctx) {
+// PFLB_BZ, 0 if not set: the planes per workgroup of the single-step kernels, which then
+// take every step
+int bz_override() {
     const char* env = getenv("PFLB_BZ");
-    if (env && atoi(env) > 0) return atoi(env);
+    return env && atoi(env) > 0 ? atoi(env) : 0;
+}
+
+int pick_bz(const Geom& G, int lattice, int nctx) {
+    if (const int bz = bz_override()) return bz;
     const long nz = G.nz;
     if (lattice == 19) {
         const long cols = (long)((G.nx + 63) / 64) * ((G.ny + 3) / 4) * nctx;
@@ -308,6 +314,8 @@ void derive(pflb_ctx* c) {
     if (tenv && atoi(tenv) >= 0 && atoi(tenv) <= 3) c->L.tile = atoi(tenv);
     c->L.bz = pick_bz(G, p.lattice, 1);
     c->L.wide = G.S > (1u << 28) - 64u;
+    c->L.fuse = p.lattice == 9 && p.storage == PFLB_STORE_FP32 && !c->L.wide && !G.open &&
+                !m.moving && !m.wetting && !bz_override();
 }
 
 int fail(pflb_ctx* c, int code, const std::string& what) {
@@ -339,11 +347,16 @@ float* phi_field(pflb_ctx* c) {
     return reinterpret_cast<float*>(static_cast<char*>(c->buf[PFLB_BUF_SCRATCH]) + scratch_bytes());
 }
 
-// one step of context c on stream st from its current buffer or layout `cur`
-hipError_t launch_one(pflb_ctx* c, const Launch& a, int cur) {
+// one launch of context c on a.stream from its current buffer or layout `cur`, of as many
+// of the `left` steps still to take as one launch takes; *took is their number, always odd,
+// so that a launch leaves the state where its steps one by one would
+hipError_t launch_some(pflb_ctx* c, const Launch& a, int cur, int left, int* took) {
+    *took = 1;
     if (c->L.inplace) return launch_step_inplace(a, c->buf[PFLB_BUF_STATE0], cur, phi_field(c));
-    return launch_step(a, c->buf[cur == 0 ? PFLB_BUF_STATE0 : PFLB_BUF_STATE1],
-                       c->buf[cur == 0 ? PFLB_BUF_STATE1 : PFLB_BUF_STATE0]);
+    const void* src = c->buf[cur == 0 ? PFLB_BUF_STATE0 : PFLB_BUF_STATE1];
+    void* dst = c->buf[cur == 0 ? PFLB_BUF_STATE1 : PFLB_BUF_STATE0];
+    *took = fused_steps(a, 1, left);
+    return *took > 1 ? launch_step_fused(a, src, dst, nullptr, 1) : launch_step(a, src, dst);
 }
 
 struct FileHeader {
@@ -581,11 +594,11 @@ int pflb_step(pflb_ctx* c, int nsteps, void* stream) {
     if (nsteps < 0) return fail(c, PFLB_ERR_PARAM, "nsteps < 0");
     Launch a = c->L;
     a.stream = (hipStream_t)stream;
-    for (int s = 0; s < nsteps; ++s) {
-        hipError_t e = launch_one(c, a, c->cur);
+    for (int s = 0, took; s < nsteps; s += took) {
+        hipError_t e = launch_some(c, a, c->cur, nsteps - s, &took);
         if (e != hipSuccess) return hip_fail(c, e, "step launch");
         c->cur ^= 1;
-        c->steps += 1;
+        c->steps += took;
     }
     return PFLB_OK;
 }
@@ -607,8 +620,8 @@ int pflb_step_graph(pflb_ctx* c, int nsteps, void* stream) {
         a.stream = st;
         int cur = c->cur;
         hipError_t le = hipSuccess;
-        for (int k = 0; k < nsteps && le == hipSuccess; ++k) {
-            le = launch_one(c, a, cur);
+        for (int k = 0, took; k < nsteps && le == hipSuccess; k += took) {
+            le = launch_some(c, a, cur, nsteps - k, &took);
             cur ^= 1;
         }
         e = hipStreamEndCapture(st, &g);
@@ -872,9 +885,11 @@ extern "C" int pflb_step_many(pflb_ctx* const* c, int n, int nsteps, void* strea
         Launch a = gr[k0]->L;
         a.stream = (hipStream_t)stream;
         a.bz = pick_bz(a.G, a.q, nb);
+        a.fuse = a.fuse && !bz_override();
         StepBatch bt;
         memset(&bt, 0, sizeof(bt));
-        for (int s = 0; s < nsteps; ++s) {
+        for (int s = 0, took; s < nsteps; s += took) {
+            took = fused_steps(a, nb, nsteps - s);
             for (int j = 0; j < nb; ++j) {
                 pflb_ctx* ck = gr[k0 + j];
                 StepEnt& e = bt.e[j];
@@ -883,11 +898,12 @@ extern "C" int pflb_step_many(pflb_ctx* const* c, int n, int nsteps, void* strea
                 e.m = ck->L.m;
                 e.cd = ck->L.cd;
             }
-            hipError_t e = launch_step_batch(a, bt, nb);
+            hipError_t e = took > 1 ? launch_step_fused(a, nullptr, nullptr, &bt, nb)
+                                    : launch_step_batch(a, bt, nb);
             if (e != hipSuccess) return hip_fail(c[0], e, "batched step launch");
             for (int j = 0; j < nb; ++j) {
                 gr[k0 + j]->cur ^= 1;
-                gr[k0 + j]->steps += 1;
+                gr[k0 + j]->steps += took;
             }
         }
     }

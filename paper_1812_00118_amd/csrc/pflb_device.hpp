@@ -1083,4 +1083,32 @@ __device__ __forceinline__ void collide_stream(const Model& m, const Macro& a, f
     out.finish();
 }
 
+// ---------------------------------------------------------------------------
+// shared by the step kernels
+// ---------------------------------------------------------------------------
+// Workgroup -> tile.  Workgroups are dispatched round-robin over the 8 XCDs (each with
+// its own L2); tile t goes to the workgroup that makes each XCD sweep a contiguous run
+// of tiles, so the y-neighbours whose halos overlap share an L2 while they run.
+__device__ __forceinline__ int xcd_tile(int b, int nblk) {
+    const int xcd = b & 7, loc = b >> 3, per = nblk >> 3, rem = nblk & 7;
+    return xcd < rem ? xcd * (per + 1) + loc : rem * (per + 1) + (xcd - rem) * per + loc;
+}
+
+// Workgroup barrier over LDS traffic only.  Inside the step no thread reads global
+// memory that another thread writes (src is read-only, dst write-only), so the global
+// stores of a finished plane may stay in flight across it; __syncthreads() would wait
+// for them (vmcnt(0)) at every plane.  The memory clobber keeps the compiler from
+// moving LDS accesses across it.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// The table of a batched step, an empty argument for the single-context kernels.
+template <bool BATCHED>
+struct StepTable {};
+template <>
+struct StepTable<true> {
+    StepBatch bt;
+};
+
 }  // namespace pflb

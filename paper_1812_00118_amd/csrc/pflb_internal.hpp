@@ -15,6 +15,7 @@ struct Launch {
     int bz;             // planes per workgroup in the fused step
     int tile;           // D3Q19 tile shape: 0: 64x4, 1: 64x8, 2: 32x8, 3: 32x4
     bool wide;          // more than 2^28 - 64 sites: 64-bit slot addresses
+    bool fuse;          // a two-dimensional FP32 domain that may take several steps a launch
     bool inplace;       // FP32 in-place storage: one state buffer, layout by step parity
     Geom G;
     Model m;
@@ -26,6 +27,12 @@ hipError_t launch_step(const Launch& a, const void* src, void* dst);
 // one step of n <= BATCH_MAX contexts without moving walls or contact angles
 // (blockIdx.y = context)
 hipError_t launch_step_batch(const Launch& a, const StepBatch& bt, int n);
+// Several steps of two-dimensional FP32 domains in one launch: how many of the `left` steps
+// still to take one launch for n contexts of a's geometry takes (1: single steps; odd), and
+// that launch (bt: a batch of n contexts, else src -> dst).
+int fused_steps(const Launch& a, int n, int left);
+hipError_t launch_step_fused(const Launch& a, const void* src, void* dst, const StepBatch* bt,
+                             int n);
 // h, g: Q arrays of stride hs (0: N) each
 hipError_t launch_equilibrium(const Launch& a, uint32_t N, const float* phi, const float* u,
                               const float* P, float* h, float* g, size_t hs = 0);

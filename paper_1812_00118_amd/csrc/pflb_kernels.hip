@@ -13,28 +13,11 @@
 
 namespace pflb {
 
-// Workgroup -> tile.  Workgroups are dispatched round-robin over the 8 XCDs (each with
-// its own L2); tile t goes to the workgroup that makes each XCD sweep a contiguous run
-// of tiles, so the y-neighbours whose halos overlap share an L2 while they run.
-__device__ __forceinline__ int xcd_tile(int b, int nblk) {
-    const int xcd = b & 7, loc = b >> 3, per = nblk >> 3, rem = nblk & 7;
-    return xcd < rem ? xcd * (per + 1) + loc : rem * (per + 1) + (xcd - rem) * per + loc;
-}
-
-// Workgroup barrier over LDS traffic only.  Inside the step no thread reads global
-// memory that another thread writes (src is read-only, dst write-only), so the global
-// stores of a finished plane may stay in flight across it; __syncthreads() would wait
-// for them (vmcnt(0)) at every plane.  The memory clobber keeps the compiler from
-// moving LDS accesses across it.
 // Keeps v computed on every lane at this point: a value used only under a per-lane
 // condition is otherwise sunk into that branch, and so are its loads
 __device__ __forceinline__ void keep(float v) { asm volatile("" ::"v"(v)); }
 __device__ __forceinline__ void keep(const uint4& w) {
     asm volatile("" ::"v"(w.x), "v"(w.y), "v"(w.z), "v"(w.w));
-}
-
-__device__ __forceinline__ void lds_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 // ---------------------------------------------------------------------------
@@ -55,13 +38,6 @@ __device__ __forceinline__ void lds_barrier() {
 // blockIdx.y picks the context, whose buffers and parameters replace src, dst, m and cd.
 // (The single-context kernel takes an empty table; the body stays in the kernel itself,
 // which compiles to measurably faster code than the same body in an inlined function.)
-template <bool BATCHED>
-struct StepTable {};
-template <>
-struct StepTable<true> {
-    StepBatch bt;
-};
-
 // The FP16S XBC variants are held to two waves per SIMD: they need a few registers
 // more than 256 and would otherwise run one wave per SIMD; the spills this costs are
 // cheaper (measured: all-wall boxes with contact angles or moving walls 1.7-1.9x faster).
