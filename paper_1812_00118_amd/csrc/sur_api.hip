@@ -112,20 +112,6 @@ const ParamLayout PL;
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-constexpr int COLSUM_PX = 1024;   // pixels per block of the primitive's bias sums
-constexpr int SILU_PX = 256;      // pixels per block of the fused SiLU backward
-
-// floats of the partial-sum buffer for one layer's weight and bias gradients
-size_t wgrad_part_floats(int B, int H, int W, int Cout, int Cin) {
-    int per;
-    const int ns = wgrad_nsplit(B, H, W, Cout, Cin, &per);
-    const size_t P = (size_t)B * H * W;
-    const size_t a = (size_t)ns * Cout * 9 * Cin;
-    const size_t b = (P + SILU_PX - 1) / SILU_PX * Cout;
-    const size_t c = (P + COLSUM_PX - 1) / COLSUM_PX * Cout;
-    return std::max(a, std::max(b, c));
-}
-
 // byte offsets into the caller's workspace
 struct Plan {
     size_t act[NBUFS], z[NL], dact[NBUFS];
@@ -313,20 +299,16 @@ int run_backward(pfsur_ctx* c, const void* x, const float* y, int B, char* ws, h
     SUR_TRY(head_bwd(reinterpret_cast<const __bf16*>(ws + p.act[D0B]), HEAD_C, 0,
                      c->master + PL.head, dout, P0, dact(D0B), HEAD_C, 0, part, st),
             "head backward");
-    SUR_TRY(reduce_splits(part, (int)head_blocks(P0), PFSUR_OUT_CH * (HEAD_C + 1),
-                          c->grad + PL.head, 0, st),
+    constexpr size_t nh = PFSUR_OUT_CH * (HEAD_C + 1);
+    SUR_TRY(reduce_splits(part, (int)head_blocks(P0), nh, nh, nh, c->grad + PL.head, nullptr, st),
             "head reduce");
     for (int l = NL - 1; l >= 0; --l) {
         const LayerDef& L = LAYERS[l];
         const int Hl = H >> L.level, Wl = W >> L.level;
         const int P = B * Hl * Wl;
-        // dz and the bias gradient's partial sums, then the weight gradient (both use part)
         SUR_TRY(silu_bwd(dact(L.out_buf), BUFS[L.out_buf].C, L.out_c0,
-                         reinterpret_cast<const __bf16*>(ws + p.z[l]), P, L.Cout, SILU_PX, dz,
-                         part, st),
+                         reinterpret_cast<const __bf16*>(ws + p.z[l]), P, L.Cout, dz, st),
                 "silu backward");
-        SUR_TRY(reduce_splits(part, (P + SILU_PX - 1) / SILU_PX, L.Cout, c->grad + PL.b[l], 0, st),
-                "bias reduce");
         WgradP wg;
         wg.g = gather_of(L, ws, p, x, H, W);
         wg.B = B;
@@ -334,12 +316,8 @@ int run_backward(pfsur_ctx* c, const void* x, const float* y, int B, char* ws, h
         wg.W = Wl;
         wg.dz = dz;
         wg.Cout = L.Cout;
-        int per;
-        const int ns = wgrad_nsplit(B, Hl, Wl, L.Cout, L.Cin, &per);
         wg.part = part;
-        SUR_TRY(wgrad(wg, st), "wgrad");
-        SUR_TRY(reduce_splits(part, ns, (size_t)L.Cout * 9 * L.Cin, c->grad + PL.w[l], 0, st),
-                "wgrad reduce");
+        SUR_TRY(wgrad(wg, c->grad + PL.w[l], c->grad + PL.b[l], st), "wgrad");
         if (l == 0) continue;
         ConvP d;
         memset(&d, 0, sizeof(d));
@@ -975,7 +953,6 @@ int pfsur_conv_wgrad(const void* x, const void* dy, int batch, int H, int W, int
         return PFLB_ERR_PARAM;
     if (!aligned16(x) || !aligned16(dy)) return PFLB_ERR_ALIGN;
     hipStream_t st = (hipStream_t)stream;
-    const int P = batch * H * W;
     WgradP a;
     a.g = plain_gather(x, H, W, Cin, mode);
     a.B = batch;
@@ -983,17 +960,8 @@ int pfsur_conv_wgrad(const void* x, const void* dy, int batch, int H, int W, int
     a.W = W;
     a.dz = static_cast<const __bf16*>(dy);
     a.Cout = Cout;
-    int per;
-    const int ns = wgrad_nsplit(batch, H, W, Cout, Cin, &per);
     a.part = static_cast<float*>(work);
-    if (wgrad(a, st) != hipSuccess) return PFLB_ERR_DEVICE;
-    if (reduce_splits(a.part, ns, (size_t)Cout * 9 * Cin, dw, 0, st) != hipSuccess)
-        return PFLB_ERR_DEVICE;
-    if (db) {
-        if (colsum(a.dz, P, Cout, COLSUM_PX, a.part, st) != hipSuccess) return PFLB_ERR_DEVICE;
-        if (reduce_splits(a.part, (P + COLSUM_PX - 1) / COLSUM_PX, Cout, db, 0, st) != hipSuccess)
-            return PFLB_ERR_DEVICE;
-    }
+    if (wgrad(a, dw, db, st) != hipSuccess) return PFLB_ERR_DEVICE;
     return PFLB_OK;
 }
 

@@ -20,7 +20,7 @@ struct GatherP {
 
 // out[p, co] for p over B x H x W output pixels, co < Cout; weights [Cout][9][C] BF16.
 // Epilogue: v = acc + bias; zout (BF16 [P][Cout]) <- v; out (BF16 at channel stride
-// out_cs, offset out_c0) <- act ? silu(v) : v; fout (FP32 at f_cs, f_c0) <- v (or += v);
+// out_cs, offset out_c0) <- act ? silu(v) : v; fout (FP32 at f_cs, f_c0) <- v;
 // pout (BF16 [B][H/2][W/2][pout_cs], channels from 0; needs out and even H, W) <- the 2x2
 // average of what out receives, as the pooling gather computes it.  head_out (FP32
 // [P][4]; 32-channel same-resolution layers only) <- the 1x1 head (head_w [4][32],
@@ -36,7 +36,7 @@ struct ConvP {
     __bf16* out;
     int out_cs, out_c0;
     float* fout;
-    int f_cs, f_c0, f_accum;
+    int f_cs, f_c0;
     __bf16* pout;
     int pout_cs;
     const float* head_w;
@@ -44,8 +44,8 @@ struct ConvP {
     float* head_out;
 };
 
-// part[split][Cout][9][C] = sum over the split's pixels of dz[p, co] in[p + off(tap), ci]
-// (splits: wgrad_nsplit)
+// sums over pixels of dz[p, co] in[p + off(tap), ci] and of dz[p, co]; part: wgrad_part_floats
+// floats of partial sums
 struct WgradP {
     GatherP g;
     int B, H, W;
@@ -71,13 +71,15 @@ hipError_t conv3x3(const ConvP& a, hipStream_t st);
 // the first two layers at inference: a0 the first (8 input channels, its outputs not
 // stored), a the second (32 -> 32 channels, same resolution)
 hipError_t conv_stem(const ConvP& a0, const ConvP& a, hipStream_t st);
-hipError_t wgrad(const WgradP& a, hipStream_t st);
-int wgrad_nsplit(int B, int H, int W, int Cout, int Cin, int* per_split);
-hipError_t reduce_splits(const float* part, int nsplit, size_t n, float* out, int acc,
-                         hipStream_t st);
-hipError_t colsum(const __bf16* m, int P, int C, int px_per_block, float* part, hipStream_t st);
-hipError_t silu_bwd(const float* dact, int cs, int c0, const __bf16* z, int P, int C, int ppb,
-                    __bf16* dz, float* part, hipStream_t st);
+// dw [Cout][9][C] and db [Cout]
+hipError_t wgrad(const WgradP& a, float* dw, float* db, hipStream_t st);
+size_t wgrad_part_floats(int B, int H, int W, int Cout, int Cin);
+// sum over the splits of part[split][i], i < n (rows of `stride`): out[i] for i < nhead, then
+// tail[i - nhead]
+hipError_t reduce_splits(const float* part, int nsplit, size_t stride, size_t n, size_t nhead,
+                         float* out, float* tail, hipStream_t st);
+hipError_t silu_bwd(const float* dact, int cs, int c0, const __bf16* z, int P, int C, __bf16* dz,
+                    hipStream_t st);
 hipError_t unpool_add(const float* dlo, int B, int Hl, int Wl, int C, float* ghi, int cs, int c0,
                       hipStream_t st);
 hipError_t sumpool(const float* dhi, int B, int Hl, int Wl, int C, float* glo, int cs, int c0,

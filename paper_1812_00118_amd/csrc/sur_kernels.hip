@@ -31,7 +31,17 @@ __device__ __forceinline__ float silu_grad(float z) {
     return s * (1.0f + z * (1.0f - s));
 }
 
+// Workgroup barrier over LDS traffic only: __syncthreads() also waits for the wave's global
+// stores to be acknowledged
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 __device__ __forceinline__ int wrap(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
+
+// coordinate of a halo position from -1 on: positions past n, which no valid output uses,
+// take that of n, so that the coordinate is in range for every n >= 1
+__device__ __forceinline__ int halo(int v, int n) { return wrap(min(v, n), n); }
 
 // 8 consecutive input channels at output-resolution pixel (b, y, x), through the layer's
 // input mode (same resolution, 2x nearest upsampling, or 2x2 average pooling).  M is the
@@ -62,6 +72,44 @@ __device__ __forceinline__ bf16x8 gather8(const GatherP& g, int b, int y, int x,
         r[k] = (__bf16)(0.25f * ((((float)v0[k] + (float)v1[k]) + (float)v2[k]) + (float)v3[k]));
     return r;
 }
+
+// Staging of an E x E halo patch of 32 channels by a workgroup of 256 threads: a thread
+// takes one (column, group of 8 channels) and every row of its own run of rows, so that a
+// load's address is the one before it plus a row (the wrap is one compare), where addressing
+// each 16-byte item by itself took 30 and more instructions.  Items lie row by row, column
+// by column, 4 groups a pixel.
+template <int E>
+struct HaloCols {
+    static constexpr int COLS = 4 * E;                    // (column, group) pairs
+    static constexpr int RUNS = 256 / COLS;               // runs of rows side by side
+    static constexpr int N = (E + RUNS - 1) / RUNS;       // rows (loads) per thread
+    int col, row0;                                        // this thread's; row0 >= E: none
+    __device__ __forceinline__ HaloCols()
+        : col((int)threadIdx.x % COLS), row0((int)threadIdx.x / COLS * N) {}
+    __device__ __forceinline__ bool has(int k) const { return row0 < RUNS * N && row0 + k < E; }
+    // loads of the patch whose first row and column are y, x (from -1 on) of image b, at
+    // channels c of the tensor g as it lies in memory; nothing past channel g.C
+    __device__ __forceinline__ void load(const GatherP& g, int b, int y, int x, int c,
+                                         bf16x8 (&r)[N]) const {
+        const int cc = c + 8 * (col & 3);
+        const size_t rowb = (size_t)g.Win * g.cs;
+        const __bf16* p = g.p + (size_t)b * g.Hin * rowb +
+                          (size_t)halo(x + (col >> 2), g.Win) * g.cs + g.c0 + cc;
+        int yy = halo(min(y + row0, g.Hin), g.Hin);
+        p += yy * rowb;
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            r[k] = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
+            if (has(k) && cc < g.C) r[k] = *reinterpret_cast<const bf16x8*>(p);
+            ++yy;
+            p += rowb;
+            if (yy == g.Hin) {
+                yy = 0;
+                p -= (size_t)g.Hin * rowb;
+            }
+        }
+    }
+};
 
 // ---------------------------------------------------------------------------
 // Implicit-GEMM 3x3 convolution.  A workgroup of 4 waves covers 256 output pixels x 32
@@ -127,7 +175,7 @@ __global__ void __launch_bounds__(256) k_conv3x3(ConvP a) {
                     a.out[(size_t)p * a.out_cs + a.out_c0 + co] = (__bf16)(a.act ? silu(v) : v);
                 if (a.fout) {
                     float* f = a.fout + (size_t)p * a.f_cs + a.f_c0 + co;
-                    *f = a.f_accum ? *f + v : v;
+                    *f = v;
                 }
             }
     }
@@ -148,6 +196,7 @@ __global__ void __launch_bounds__(256) k_conv3x3(ConvP a) {
 // ---------------------------------------------------------------------------
 constexpr int TP = 16;                 // output patch edge
 constexpr int HP = TP + 2;             // halo patch edge
+constexpr int UPH = TP / 2 + 2;        // the same at half resolution (an upsampled input)
 constexpr int APAD = 40;               // BF16 per staged pixel (32 channels + pad)
 constexpr int BPAD = 9 * 32 + 8;       // BF16 per staged output channel
 // Row pitch of the staged halo patch: HP pixels of APAD BF16 plus RPAD BF16, so that a
@@ -159,58 +208,85 @@ constexpr int BPAD = 9 * 32 + 8;       // BF16 per staged output channel
 // are exactly the ones the first row leaves free.
 constexpr int RPAD = 176;
 constexpr int ROWA = HP * APAD + RPAD; // BF16 per staged patch row
-constexpr int A_ITEMS = HP * HP * 4;   // 16-byte items of the halo patch
-constexpr int A_PER_T = (A_ITEMS + 255) / 256;
 
 // Epilogues of a 16x16-pixel tile.  The MFMAs compute D[channel][pixel] (weights as the
 // A operand), so lane l holds pixel l%32 of its 32-pixel row block and, for j = 0..15,
 // channel 8(j/4) + 4(l/32) + j%4 of the 32-channel block.
 //
+// The bias comes from LDS (sBias, the workgroup's output channels, zeros without a bias): as
+// per-lane loads from memory, each behind its own wait, it was the largest part of the
+// epilogue (see k_conv_tiled).
+//
+// values of row block mb, channel block nb: 4 runs of 4 channels
+template <int NB, int MB>
+__device__ __forceinline__ void tile_values(const f32x16 (&acc)[MB][NB], int mb, int nb, int g,
+                                            const float* sBias, float (&v)[16]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const float4 b = *reinterpret_cast<const float4*>(&sBias[nb * 32 + 8 * q + 4 * g]);
+        v[4 * q] = acc[mb][nb][4 * q] + b.x;
+        v[4 * q + 1] = acc[mb][nb][4 * q + 1] + b.y;
+        v[4 * q + 2] = acc[mb][nb][4 * q + 2] + b.z;
+        v[4 * q + 3] = acc[mb][nb][4 * q + 3] + b.w;
+    }
+}
+
+// 16 values as BF16, through SiLU if act is set
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void to_bf16(const float (&v)[16], int act, bf16x4 (&o)[4]) {
+    if (act) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o[e >> 2][e & 3] = (__bf16)silu(v[e]);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) o[e >> 2][e & 3] = (__bf16)v[e];
+    }
+}
+
+// FP32 output of one pixel's 32-channel block
+__device__ __forceinline__ void put_f32(const ConvP& a, size_t p, int cb, int g,
+                                        const float (&v)[16]) {
+    float* f = a.fout + p * a.f_cs + a.f_c0 + cb + 4 * g;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<float4*>(f + 8 * q) =
+            make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+}
+
 // Direct: each lane writes its runs of 4 consecutive channels as one 8-byte (BF16) or
 // 16-byte (FP32) store.  Used for 32-channel tiles, where it measured as fast as the
 // staged form without its extra barrier.
 template <int NB>
 __device__ __forceinline__ void tile_epilogue_direct(const ConvP& a, const f32x16 (&acc)[2][NB],
                                                      int b, int y0, int x0, int co0, int wave,
-                                                     int l32, int g) {
-    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+                                                     int l32, int g, const float* sBias) {
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb) {
         const int y = y0 + 4 * wave + 2 * mb + (l32 >> 4), x = x0 + (l32 & 15);
         if (y >= a.H || x >= a.W) continue;
         const size_t p = ((size_t)b * a.H + y) * a.W + x;
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
+        for (int nb = 0; nb < NB; ++nb) {
+            const int cb = co0 + nb * 32;
+            if (cb >= a.Cout) break;
+            float v[16];
+            bf16x4 o[4];
+            tile_values(acc, mb, nb, g, sBias, v);
+            if (a.zout) {
+                to_bf16(v, 0, o);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int co = co0 + nb * 32 + 8 * q + 4 * g;   // first of 4 channels
-                if (co >= a.Cout) continue;
-                float v[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    v[e] = acc[mb][nb][4 * q + e] + (a.bias ? a.bias[co + e] : 0.0f);
-                if (a.zout) {
-                    bf16x4 z;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) z[e] = (__bf16)v[e];
-                    *reinterpret_cast<bf16x4*>(a.zout + p * a.Cout + co) = z;
-                }
-                if (a.out) {
-                    bf16x4 o;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) o[e] = (__bf16)(a.act ? silu(v[e]) : v[e]);
-                    *reinterpret_cast<bf16x4*>(a.out + p * a.out_cs + a.out_c0 + co) = o;
-                }
-                if (a.fout) {
-                    float4* f = reinterpret_cast<float4*>(a.fout + p * a.f_cs + a.f_c0 + co);
-                    float4 w = make_float4(v[0], v[1], v[2], v[3]);
-                    if (a.f_accum) {
-                        const float4 o = *f;
-                        w.x += o.x; w.y += o.y; w.z += o.z; w.w += o.w;
-                    }
-                    *f = w;
-                }
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<bf16x4*>(a.zout + p * a.Cout + cb + 8 * q + 4 * g) = o[q];
             }
+            if (a.out) {
+                to_bf16(v, a.act, o);
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<bf16x4*>(a.out + p * a.out_cs + a.out_c0 + cb + 8 * q +
+                                               4 * g) = o[q];
+            }
+            if (a.fout) put_f32(a, p, cb, g, v);
+        }
     }
 }
 
@@ -231,36 +307,22 @@ __device__ __forceinline__ void wave_lds_sync() { asm volatile("s_waitcnt lgkmcn
 template <int NB>
 __device__ __forceinline__ void tile_epilogue_staged(const ConvP& a, const f32x16 (&acc)[2][NB],
                                                      int b, int y0, int x0, int co0, int wave,
-                                                     int l32, int g, __bf16* __restrict__ sO) {
-    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+                                                     int l32, int g, const float* sBias,
+                                                     __bf16* __restrict__ sO) {
     const int lane = l32 + 32 * g;
     __bf16* so = sO + wave * 64 * OROW;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
         const int cb = co0 + nb * 32;            // first channel of the block
         if (cb >= a.Cout) break;
-        // value of channel run q (4 channels), element e, row block mb
-        auto val = [&](int mb, int q, int e) {
-            return acc[mb][nb][4 * q + e] + (a.bias ? a.bias[cb + 8 * q + 4 * g + e] : 0.0f);
-        };
+        float v[2][16];
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb) tile_values(acc, mb, nb, g, sBias, v[mb]);
         if (a.fout) {
 #pragma unroll
             for (int mb = 0; mb < 2; ++mb) {
                 const int y = y0 + 4 * wave + 2 * mb + (l32 >> 4), x = x0 + (l32 & 15);
-                if (y >= a.H || x >= a.W) continue;
-                const size_t p = ((size_t)b * a.H + y) * a.W + x;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    float4* f = reinterpret_cast<float4*>(a.fout + p * a.f_cs + a.f_c0 + cb +
-                                                          8 * q + 4 * g);
-                    float4 w = make_float4(val(mb, q, 0), val(mb, q, 1), val(mb, q, 2),
-                                           val(mb, q, 3));
-                    if (a.f_accum) {
-                        const float4 o = *f;
-                        w.x += o.x; w.y += o.y; w.z += o.z; w.w += o.w;
-                    }
-                    *f = w;
-                }
+                if (y < a.H && x < a.W) put_f32(a, ((size_t)b * a.H + y) * a.W + x, cb, g, v[mb]);
             }
         }
 #pragma unroll
@@ -269,19 +331,14 @@ __device__ __forceinline__ void tile_epilogue_staged(const ConvP& a, const f32x1
             if (!dst) continue;
             const int cs = pass == 0 ? a.Cout : a.out_cs;
             const int c0 = pass == 0 ? 0 : a.out_c0;
-            const bool act = pass == 1 && a.act;
 #pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
+            for (int mb = 0; mb < 2; ++mb) {
+                bf16x4 o[4];
+                to_bf16(v[mb], pass == 1 && a.act, o);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    bf16x4 o;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float t = val(mb, q, e);
-                        o[e] = (__bf16)(act ? silu(t) : t);
-                    }
-                    *reinterpret_cast<bf16x4*>(&so[(mb * 32 + l32) * OROW + 8 * q + 4 * g]) = o;
-                }
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<bf16x4*>(&so[(mb * 32 + l32) * OROW + 8 * q + 4 * g]) = o[q];
+            }
             wave_lds_sync();
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -345,19 +402,16 @@ __device__ __forceinline__ void head_half(const float (&v)[16], int g, const flo
 // is never written.  sH holds the head's weights and biases.
 __device__ __forceinline__ void tile_epilogue_head(const ConvP& a, const f32x16 (&acc)[2][1],
                                                    int b, int y0, int x0, int wave, int l32,
-                                                   int g, const float* sH) {
+                                                   int g, const float* sBias, const float* sH) {
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb) {
         const int y = y0 + 4 * wave + 2 * mb + (l32 >> 4), x = x0 + (l32 & 15);
         float v[16];
+        bf16x4 r[4];
+        tile_values(acc, mb, 0, g, sBias, v);
+        to_bf16(v, a.act, r);
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int co = 8 * q + 4 * g + e;
-                const float t = acc[mb][0][4 * q + e] + (a.bias ? a.bias[co] : 0.0f);
-                v[4 * q + e] = (float)(__bf16)(a.act ? silu(t) : t);
-            }
+        for (int e = 0; e < 16; ++e) v[e] = (float)r[e >> 2][e & 3];
         float p[4], o[4];
         head_half(v, g, sH, p);
 #pragma unroll
@@ -380,8 +434,6 @@ enum { EPI_DIRECT = 0, EPI_STAGED = 1, EPI_HEAD = 2 };
 template <int NT, int MODE, int EPI>
 __global__ void __launch_bounds__(256, (NT == 32 && EPI != EPI_HEAD) ? 3 : 2)
 k_conv_tiled(ConvP a, int tiles_per_wg) {
-    constexpr int B_ITEMS = NT * 36;             // 16-byte items of the weight tile
-    constexpr int B_PER_T = (B_ITEMS + 255) / 256;
     constexpr int NB = NT / 32;
     __shared__ __align__(16) __bf16 sA[HP * ROWA];
     __shared__ __align__(16) __bf16 sB[NT * BPAD];
@@ -389,6 +441,10 @@ k_conv_tiled(ConvP a, int tiles_per_wg) {
     static_assert((ROWA * 2 / 16) % 32 == 16, "patch rows 16 mod 32 16-byte units apart");
     static_assert(EPI != EPI_HEAD || (NT == 32 && MODE == MODE_SAME), "head fusion: 32 channels");
     __shared__ float sH[EPI == EPI_HEAD ? 4 * 32 + 4 : 1];
+    __shared__ __align__(16) float sBias[NT];
+    if (threadIdx.x < NT)   // ordered before use by the first tile's barriers, as sH
+        sBias[threadIdx.x] = a.bias && (int)(blockIdx.y * NT + threadIdx.x) < a.Cout
+                                 ? a.bias[blockIdx.y * NT + threadIdx.x] : 0.0f;
     if constexpr (EPI == EPI_HEAD) {   // ordered before use by the first tile's barriers
         for (int i = threadIdx.x; i < 4 * 32 + 4; i += 256)
             sH[i] = i < 128 ? a.head_w[i] : a.head_b[i - 128];
@@ -405,7 +461,6 @@ k_conv_tiled(ConvP a, int tiles_per_wg) {
     // the (tile, chunk) pairs of this workgroup, in order; with one chunk the weights
     // are staged once
     const int niter = (t_end - t_beg) * nchunk;
-    const bf16x8 zero8 = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
 
     auto tile_xy = [&](int t, int& b, int& y0, int& x0) {
         const int tx = t % tx_n;
@@ -416,58 +471,64 @@ k_conv_tiled(ConvP a, int tiles_per_wg) {
         y0 = ty * TP;
     };
 
-    bf16x8 ra[A_PER_T], rb[B_PER_T];
+    // The weights go a tap (64 channels) or two (32) at a time, 4 groups of 8 input channels
+    // an output channel.
+    constexpr int XE = MODE == MODE_UP ? UPH : HP;   // an upsampled input is staged as it lies
+    constexpr int TSTEP = 64 / NT;                   // taps a load of the workgroup covers
+    constexpr int B_PER_T = (9 + TSTEP - 1) / TSTEP;
+    const HaloCols<XE> hc;
+    const int bcol = (threadIdx.x >> 2) % NT, btap = (threadIdx.x >> 2) / NT;
+    bf16x8 ra[hc.N], rb[B_PER_T];
     auto load_a = [&](int it) {
         int b, y0, x0;
         tile_xy(t_beg + it / nchunk, b, y0, x0);
         const int c0 = (it % nchunk) * 32;
+        if constexpr (MODE == MODE_UP) {
+            hc.load(a.g, b, y0 / 2 - 1, x0 / 2 - 1, c0, ra);
+        } else if constexpr (MODE == MODE_SAME) {
+            hc.load(a.g, b, y0 - 1, x0 - 1, c0, ra);
+        } else {
 #pragma unroll
-        for (int k = 0; k < A_PER_T; ++k) {
-            const int i = threadIdx.x + 256 * k;
-            if (i < A_ITEMS) {
-                const int pi = i >> 2, grp = i & 3;
-                const int py = pi / HP, px = pi - py * HP;
-                ra[k] = gather8<MODE>(a.g, b, wrap(y0 - 1 + py, a.H), wrap(x0 - 1 + px, a.W),
-                                c0 + 8 * grp);
-            }
+            for (int k = 0; k < hc.N; ++k)
+                if (hc.has(k))
+                    ra[k] = gather8<MODE>(a.g, b, halo(y0 - 1 + hc.row0 + k, a.H),
+                                          halo(x0 - 1 + (hc.col >> 2), a.W), c0 + 8 * (hc.col & 3));
         }
     };
     auto store_a = [&]() {
 #pragma unroll
-        for (int k = 0; k < A_PER_T; ++k) {
-            const int i = threadIdx.x + 256 * k;
-            if (i < A_ITEMS) {
-                const int pi = i >> 2, py = pi / HP, px = pi - py * HP;
-                *reinterpret_cast<bf16x8*>(&sA[py * ROWA + px * APAD + 8 * (i & 3)]) = ra[k];
-            }
-        }
+        for (int k = 0; k < hc.N; ++k)
+            if (hc.has(k))
+                *reinterpret_cast<bf16x8*>(&sA[(hc.row0 + k) * ROWA + (hc.col >> 2) * APAD +
+                                               8 * (hc.col & 3)]) = ra[k];
     };
     auto load_b = [&](int it) {
-        const int c0 = (it % nchunk) * 32;
+        const __bf16* w = a.w + ((size_t)(co0 + bcol) * 9 + btap) * C + (it % nchunk) * 32 +
+                          8 * (threadIdx.x & 3);
 #pragma unroll
-        for (int k = 0; k < B_PER_T; ++k) {
-            const int i = threadIdx.x + 256 * k;
-            const int col = i / 36, rem = i - col * 36;
-            const int tap = rem >> 2, grp = rem & 3;
-            const int co = co0 + col;
-            rb[k] = (i < B_ITEMS && co < a.Cout)
-                        ? *reinterpret_cast<const bf16x8*>(a.w + ((size_t)co * 9 + tap) * C +
-                                                           c0 + 8 * grp)
-                        : zero8;
-        }
+        for (int k = 0; k < B_PER_T; ++k)
+            if (TSTEP * k + btap < 9) rb[k] = *reinterpret_cast<const bf16x8*>(w + (size_t)k * TSTEP * C);
     };
     auto store_b = [&]() {
 #pragma unroll
-        for (int k = 0; k < B_PER_T; ++k) {
-            const int i = threadIdx.x + 256 * k;
-            const int col = i / 36, rem = i - col * 36;
-            if (i < B_ITEMS) *reinterpret_cast<bf16x8*>(&sB[col * BPAD + rem * 8]) = rb[k];
-        }
+        for (int k = 0; k < B_PER_T; ++k)
+            if (TSTEP * k + btap < 9)
+                *reinterpret_cast<bf16x8*>(&sB[bcol * BPAD + (TSTEP * k + btap) * 32 +
+                                               8 * (threadIdx.x & 3)]) = rb[k];
     };
 
     f32x16 acc[2][NB];
     // this lane's pixel in each row block: patch row 4w + 2mb + l32/16, column l32%16
     const int prow = 4 * wave + (l32 >> 4), pcol = l32 & 15;
+    // where it reads its operands: halo position (prow + 2 mb + dy, pcol + dx), for an
+    // upsampled input that position halved, (v + 1) >> 1 (prow - l32/16 is even: tap row 0
+    // reads the lane's own row, 1 the middle one of all, 2 the one after the lane's own)
+    const __bf16* pa[2][2];
+#pragma unroll
+    for (int odd = 0; odd < 2; ++odd) {
+        pa[0][odd] = &sA[(2 * wave + (l32 >> 4)) * ROWA + ((pcol + odd + 1) >> 1) * APAD + 8 * g];
+        pa[1][odd] = &sA[(2 * wave + 1) * ROWA + ((pcol + odd + 1) >> 1) * APAD + 8 * g];
+    }
 
     if (niter > 0) {
         load_b(0);
@@ -501,7 +562,9 @@ k_conv_tiled(ConvP a, int tiles_per_wg) {
 #pragma unroll
             for (int mb = 0; mb < 2; ++mb)
                 A[mb] = *reinterpret_cast<const bf16x8*>(
-                    &sA[(prow + 2 * mb + dy) * ROWA + (pcol + dx) * APAD + 16 * h + 8 * g]);
+                    MODE == MODE_UP
+                        ? pa[dy & 1][dx & 1] + (mb + (dy >> 1)) * ROWA + (dx >> 1) * APAD + 16 * h
+                        : &sA[(prow + 2 * mb + dy) * ROWA + (pcol + dx) * APAD + 16 * h + 8 * g]);
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
                 Bm[nb] = *reinterpret_cast<const bf16x8*>(
@@ -533,11 +596,11 @@ k_conv_tiled(ConvP a, int tiles_per_wg) {
             tile_xy(t_beg + it / nchunk, b, y0, x0);
             if constexpr (EPI == EPI_STAGED) {
                 __syncthreads();                 // every wave is done reading the patch
-                tile_epilogue_staged<NB>(a, acc, b, y0, x0, co0, wave, l32, g, sA);
+                tile_epilogue_staged<NB>(a, acc, b, y0, x0, co0, wave, l32, g, sBias, sA);
             } else if constexpr (EPI == EPI_HEAD) {
-                tile_epilogue_head(a, acc, b, y0, x0, wave, l32, g, sH);
+                tile_epilogue_head(a, acc, b, y0, x0, wave, l32, g, sBias, sH);
             } else {
-                tile_epilogue_direct<NB>(a, acc, b, y0, x0, co0, wave, l32, g);
+                tile_epilogue_direct<NB>(a, acc, b, y0, x0, co0, wave, l32, g, sBias);
             }
         }
     }
@@ -553,6 +616,9 @@ constexpr int BPAD1 = 88;   // 10 taps x 8 channels + pad: conflict-free 16-byte
 __global__ void __launch_bounds__(256, 2) k_conv_first(ConvP a) {
     __shared__ __align__(16) __bf16 sA[HP * HP * 8];
     __shared__ __align__(16) __bf16 sB[32 * BPAD1];
+    __shared__ __align__(16) float sBias[32];
+    if (threadIdx.x < 32)
+        sBias[threadIdx.x] = a.bias ? a.bias[blockIdx.y * 32 + threadIdx.x] : 0.0f;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l32 = lane & 31, g = lane >> 5;
     const int tx_n = (a.W + TP - 1) / TP, ty_n = (a.H + TP - 1) / TP;
@@ -567,7 +633,7 @@ __global__ void __launch_bounds__(256, 2) k_conv_first(ConvP a) {
     for (int it = threadIdx.x; it < HP * HP; it += 256) {
         const int py = it / HP, px = it - py * HP;
         *reinterpret_cast<bf16x8*>(&sA[it * 8]) =
-            gather8<MODE_SAME>(a.g, b, wrap(y0 - 1 + py, a.H), wrap(x0 - 1 + px, a.W), 0);
+            gather8<MODE_SAME>(a.g, b, halo(y0 - 1 + py, a.H), halo(x0 - 1 + px, a.W), 0);
     }
     for (int it = threadIdx.x; it < 32 * 10; it += 256) {
         const int col = it / 10, tap = it - col * 10;
@@ -598,7 +664,7 @@ __global__ void __launch_bounds__(256, 2) k_conv_first(ConvP a) {
             acc[mb][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Bm, A, acc[mb][0], 0, 0, 0);
         }
     }
-    tile_epilogue_direct<1>(a, acc, b, y0, x0, co0, wave, l32, g);
+    tile_epilogue_direct<1>(a, acc, b, y0, x0, co0, wave, l32, g, sBias);
 }
 
 // ---------------------------------------------------------------------------
@@ -624,6 +690,11 @@ __global__ void __launch_bounds__(256, 2) k_conv_stem(ConvP a0, ConvP a, int til
     __shared__ __align__(16) __bf16 sX[HP2 * HP2 * 8];
     __shared__ __align__(16) __bf16 sA[HP * ROWA];
     static_assert(4 * 64 * OROW <= HP * ROWA, "epilogue staging must fit the patch buffer");
+    __shared__ __align__(16) float sBias[64];          // of the first layer, then the second
+    if (threadIdx.x < 64) {
+        const float* b = threadIdx.x < 32 ? a0.bias : a.bias;
+        sBias[threadIdx.x] = b ? b[threadIdx.x & 31] : 0.0f;
+    }
     constexpr int X_PER_T = (HP2 * HP2 + 255) / 256;   // 16-byte input items per thread
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l32 = lane & 31, g = lane >> 5;
@@ -704,18 +775,14 @@ __global__ void __launch_bounds__(256, 2) k_conv_stem(ConvP a0, ConvP a, int til
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Bm, A, acc, 0, 0, 0);
             }
             if (p < STEM_PIX) {
-                typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+                float v[16];
+                bf16x4 o[4];
+                const f32x16 one[1][1] = {{acc}};
+                tile_values(one, 0, 0, g, sBias, v);
+                to_bf16(v, a0.act, o);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    bf16x4 o;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float v =
-                            acc[4 * q + e] + (a0.bias ? a0.bias[8 * q + 4 * g + e] : 0.0f);
-                        o[e] = (__bf16)(a0.act ? silu(v) : v);
-                    }
-                    *reinterpret_cast<bf16x4*>(&sA[py * ROWA + px * APAD + 8 * q + 4 * g]) = o;
-                }
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<bf16x4*>(&sA[py * ROWA + px * APAD + 8 * q + 4 * g]) = o[q];
             }
         }
         __syncthreads();
@@ -754,44 +821,73 @@ __global__ void __launch_bounds__(256, 2) k_conv_stem(ConvP a0, ConvP a, int til
             }
         }
         __syncthreads();                 // every wave is done reading the patch
-        tile_epilogue_staged<1>(a, acc, b, y0, x0, 0, wave, l32, g, sA);
+        tile_epilogue_staged<1>(a, acc, b, y0, x0, 0, wave, l32, g, sBias + 32, sA);
     }
 }
 
 // ---------------------------------------------------------------------------
-// Weight gradient staged through LDS: dW[o, tap, c] = sum_p dz[p, o] in[p + off(tap), c].
-// A workgroup owns 32 output x 32 input channels and all 9 taps, and a contiguous range
-// of 16x16 pixel patches (split K).  Per patch, dz is staged transposed ([o][pixel]) and
-// the input halo as three copies shifted by dx ([dx][c][halo row][16 pixels]), so every
-// MFMA operand (8 consecutive pixels of one channel) is an aligned 16-byte LDS read.
-// Wave w reduces over patch rows 4w..4w+3 for all taps; the 4 wave sums are added in a
-// fixed order and the workgroup's partial sums go to part[split].
+// Weight gradient staged through LDS: dW[o, tap, c] = sum_p dz[p, o] in[p + off(tap), c], and
+// with it the bias gradient sum_p dz[p, o].  A workgroup owns 32 output x 32 input channels
+// and all 9 taps, and a contiguous range of 16x16 pixel patches (split K).  A patch's dz and
+// input halo are staged as they lie in memory, 32 channels (64 bytes) a pixel; the products
+// sum over pixels, so each operand (8 pixels of one channel per lane) is read with gfx950's
+// transposing LDS reads, at any pixel offset: no transposed or shifted copies.  Wave w
+// reduces over patch rows 4w..4w+3; it reads each input row once for the three dy that use
+// it (22 operand reads per 36 MFMAs).  The bias is a tenth product with a matrix of ones, in
+// the workgroups of input channels 0..31.  The 4 wave sums are added in a fixed order and
+// the workgroup's sums go to part[split].  Bound by the matrix cores together with the L2
+// reads (37 KB a patch) and their latency; the form before this one transposed through 176 two-byte LDS
+// writes per thread and patch and ran the layer 64 -> 64 on 16x128x128 in 76 us; this one
+// takes 35 us (0.55 PFLOP/s; 19 GFLOP), of which the matrix cores are busy 9.
 // ---------------------------------------------------------------------------
-constexpr int DZ_STRIDE = 264;                 // 256 pixels + pad per output channel
-constexpr int XC_STRIDE = HP * 16 + 8;         // 18 halo rows x 16 pixels + pad per channel
-constexpr int X_COPY = 32 * XC_STRIDE;         // one dx-shifted copy
+// Operand of a product over 16 consecutive pixels: lane l gets pixels 8(l/32)..+7 of channel
+// l%32 from pixel-major LDS of 64 bytes a pixel.  A transposing read takes, in each group of
+// 16 lanes, 4 pixels x 16 channels (lane i of the group supplies pixel i/4, channels
+// 4(i%4)..+3) and returns to lane i the 4 pixels of channel i.  p: the lane's own address for
+// the first 4 pixels; the next 4 are `next` BF16 further.
+__device__ __forceinline__ bf16x8 read_pixels(const __bf16* p, int next) {
+    typedef __attribute__((address_space(3))) bf16x4* lds4;
+    const bf16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds4)(p));
+    const bf16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds4)(p + next));
+    return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+constexpr int RED_STRIDE = 33;                 // floats per output channel of a wave's sums
 
 template <int MODE>
 __global__ void __launch_bounds__(256, 2) k_wgrad_tiled(WgradP a, int patches_per_split,
-                                                        int npatch) {
-    __shared__ __bf16 sD[32 * DZ_STRIDE];
-    __shared__ __bf16 sX[3 * X_COPY];
+                                                        int npatch, int nsplit) {
+    // the halo of an upsampled input is staged at its own resolution
+    constexpr int XE = MODE == MODE_UP ? UPH : HP;
+    __shared__ __align__(16) __bf16 sD[TP * TP * 32];
+    __shared__ __align__(16) __bf16 sX[XE * XE * 32];
+    __shared__ float red[4 * 32 * RED_STRIDE];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l32 = lane & 31, g = lane >> 5;
-    const int o0 = blockIdx.x * 32, c0 = blockIdx.y * 32;
     const int C = a.g.C;
+    // workgroup -> (split, channel pair): all pairs of a split on one XCD (workgroups go
+    // round the 8 XCDs), so that a patch comes from memory once and then from that XCD's L2
+    const int no = (a.Cout + 31) / 32, npair = no * ((C + 31) / 32);
+    const int split = (blockIdx.x >> 3) / npair * 8 + (blockIdx.x & 7);
+    const int pair = (blockIdx.x >> 3) % npair;
+    if (split >= nsplit) return;
+    const int o0 = pair % no * 32, c0 = pair / no * 32;
     const int tx_n = (a.W + TP - 1) / TP, ty_n = (a.H + TP - 1) / TP;
-    const int pbeg = blockIdx.z * patches_per_split;
+    const int pbeg = split * patches_per_split;
     const int pend = min(npatch, pbeg + patches_per_split);
     const bf16x8 zero8 = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
+    const bool with_bias = c0 == 0;
 
-    f32x16 acc[9];
+    f32x16 acc[9], accb;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) accb[j] = 0.0f;
 #pragma unroll
     for (int t = 0; t < 9; ++t)
 #pragma unroll
         for (int j = 0; j < 16; ++j) acc[t][j] = 0.0f;
 
-    bf16x8 rd[4], rx[A_PER_T];
+    const HaloCols<XE> hc;
+    bf16x8 rd[4], rx[hc.N];
     auto load = [&](int patch) {
         int q = patch;
         const int tx = q % tx_n;
@@ -799,167 +895,158 @@ __global__ void __launch_bounds__(256, 2) k_wgrad_tiled(WgradP a, int patches_pe
         const int ty = q % ty_n;
         const int b = q / ty_n;
         const int x0 = tx * TP, y0 = ty * TP;
+        // dz: wave w stages rows 4w..4w+3, a lane one (pixel, group) of each
+        const int x = x0 + (lane >> 2), o = o0 + 8 * (lane & 3);
+        const bool in = x < a.W && o < a.Cout;
+        const __bf16* d = a.dz + (((size_t)b * a.H + y0 + 4 * wave) * a.W + x) * a.Cout + o;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const int it = threadIdx.x + 256 * k;     // 256 pixels x 4 groups of 8 channels
-            const int pi = it >> 2, og = it & 3;
-            const int y = y0 + (pi >> 4), x = x0 + (pi & 15), o = o0 + 8 * og;
-            rd[k] = (y < a.H && x < a.W && o < a.Cout)
-                        ? *reinterpret_cast<const bf16x8*>(
-                              a.dz + (((size_t)b * a.H + y) * a.W + x) * a.Cout + o)
-                        : zero8;
+            rd[k] = zero8;
+            if (in && y0 + 4 * wave + k < a.H) rd[k] = *reinterpret_cast<const bf16x8*>(d);
+            d += (size_t)a.W * a.Cout;
         }
+        if constexpr (MODE == MODE_UP) {
+            hc.load(a.g, b, y0 / 2 - 1, x0 / 2 - 1, c0, rx);
+        } else if constexpr (MODE == MODE_SAME) {
+            hc.load(a.g, b, y0 - 1, x0 - 1, c0, rx);
+        } else {
+            const int c = c0 + 8 * (hc.col & 3);
 #pragma unroll
-        for (int k = 0; k < A_PER_T; ++k) {
-            const int it = threadIdx.x + 256 * k;     // 18x18 halo pixels x 4 groups
-            if (it < A_ITEMS) {
-                const int pi = it >> 2, cg = it & 3;
-                const int hy = pi / HP, hx = pi - hy * HP;
-                const int c = c0 + 8 * cg;
-                rx[k] = c < C ? gather8<MODE>(a.g, b, wrap(y0 - 1 + hy, a.H), wrap(x0 - 1 + hx, a.W), c)
-                              : zero8;
-            }
+            for (int k = 0; k < hc.N; ++k)
+                rx[k] = hc.has(k) && c < C
+                            ? gather8<MODE>(a.g, b, halo(y0 - 1 + hc.row0 + k, a.H),
+                                            halo(x0 - 1 + (hc.col >> 2), a.W), c)
+                            : zero8;
         }
     };
     auto store = [&]() {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int it = threadIdx.x + 256 * k;
-            const int pi = it >> 2, og = it & 3;
+        for (int k = 0; k < 4; ++k)
+            *reinterpret_cast<bf16x8*>(&sD[((4 * wave + k) * TP * 4 + lane) * 8]) = rd[k];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) sD[(8 * og + e) * DZ_STRIDE + pi] = rd[k][e];
-        }
-#pragma unroll
-        for (int k = 0; k < A_PER_T; ++k) {
-            const int it = threadIdx.x + 256 * k;
-            if (it < A_ITEMS) {
-                const int pi = it >> 2, cg = it & 3;
-                const int hy = pi / HP, hx = pi - hy * HP;
-#pragma unroll
-                for (int dx = 0; dx < 3; ++dx) {
-                    const int px = hx - dx;
-                    if (px >= 0 && px < TP)
-#pragma unroll
-                        for (int e = 0; e < 8; ++e)
-                            sX[dx * X_COPY + (8 * cg + e) * XC_STRIDE + hy * 16 + px] = rx[k][e];
-                }
-            }
-        }
+        for (int k = 0; k < hc.N; ++k)
+            if (hc.has(k))
+                *reinterpret_cast<bf16x8*>(&sX[((hc.row0 + k) * hc.COLS + hc.col) * 8]) = rx[k];
     };
+    // this lane's pixel (of the first 4) and channel in a transposing read
+    const int pk = 8 * g + ((lane & 15) >> 2), ck = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+    const __bf16* dzp = &sD[(4 * wave * TP + pk) * 32 + ck];
+    const __bf16* xp[3];
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx)
+        xp[dx] = MODE == MODE_UP ? &sX[(2 * wave * UPH + ((pk + dx + 1) >> 1)) * 32 + ck]
+                                 : &sX[(4 * wave * HP + pk + dx) * 32 + ck];
+    bf16x8 ones;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
 
     if (pbeg < pend) load(pbeg);
     for (int patch = pbeg; patch < pend; ++patch) {
-        __syncthreads();
+        lds_barrier();
         store();
-        __syncthreads();
+        lds_barrier();
         if (patch + 1 < pend) load(patch + 1);
+        bf16x8 A[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int py = 4 * wave + r;
-            const bf16x8 A = *reinterpret_cast<const bf16x8*>(&sD[l32 * DZ_STRIDE + py * 16 + 8 * g]);
+        for (int r = 0; r < 4; ++r) A[r] = read_pixels(dzp + r * TP * 32, 4 * 32);
+        if (with_bias)
 #pragma unroll
-            for (int tap = 0; tap < 9; ++tap) {
-                const int dy = tap / 3, dx = tap % 3;
-                const bf16x8 Bv = *reinterpret_cast<const bf16x8*>(
-                    &sX[dx * X_COPY + l32 * XC_STRIDE + (py + dy) * 16 + 8 * g]);
-                acc[tap] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, Bv, acc[tap], 0, 0, 0);
+            for (int r = 0; r < 4; ++r)
+                accb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[r], ones, accb, 0, 0, 0);
+        // halo rows 4w + i: output row r uses row i = r + dy for tap row dy
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            bf16x8 Bv[3];
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx)
+                Bv[dx] = MODE == MODE_UP ? read_pixels(xp[dx] + ((i + 1) >> 1) * UPH * 32, 2 * 32)
+                                         : read_pixels(xp[dx] + i * HP * 32, 4 * 32);
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy) {
+                const int r = i - dy;
+                if (r < 0 || r > 3) continue;
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx)
+                    acc[3 * dy + dx] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        A[r], Bv[dx], acc[3 * dy + dx], 0, 0, 0);
             }
         }
     }
-    // fixed-order sum of the 4 waves, one tap at a time, through the (now free) sX region
-    float* red = reinterpret_cast<float*>(sX);       // [4 waves][32 o][33]
-    for (int tap = 0; tap < 9; ++tap) {
-        __syncthreads();
+    // fixed-order sum of the 4 waves, one tap (then the bias) at a time: part[split] holds
+    // [Cout][9][C], then [Cout].  (Barriers that wait for each tap's stores measured
+    // 12% slower over the network's layers.)
+    float* part = a.part + (size_t)split * ((size_t)a.Cout * 9 * C + a.Cout);
+    auto put = [&](const f32x16& v, auto&& store_at) {
+        lds_barrier();
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int o = 8 * (j >> 2) + 4 * g + (j & 3);
-            red[(wave * 32 + o) * 33 + l32] = acc[tap][j];
-        }
-        __syncthreads();
+        for (int j = 0; j < 16; ++j)
+            red[(wave * 32 + 8 * (j >> 2) + 4 * g + (j & 3)) * RED_STRIDE + l32] = v[j];
+        lds_barrier();
         for (int k = threadIdx.x; k < 1024; k += 256) {
             const int o = k >> 5, c = k & 31;
-            const float v = ((red[o * 33 + c] + red[(32 + o) * 33 + c]) + red[(64 + o) * 33 + c]) +
-                            red[(96 + o) * 33 + c];
-            if (o0 + o < a.Cout && c0 + c < C)
-                a.part[(size_t)blockIdx.z * a.Cout * 9 * C + ((size_t)(o0 + o) * 9 + tap) * C + c0 + c] = v;
+            const float* r = red + o * RED_STRIDE + c;
+            store_at(o, c, ((r[0] + r[32 * RED_STRIDE]) + r[64 * RED_STRIDE]) + r[96 * RED_STRIDE]);
         }
-    }
+    };
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap)
+        put(acc[tap], [&](int o, int c, float v) {
+            if (o0 + o < a.Cout && c0 + c < C)
+                part[((size_t)(o0 + o) * 9 + tap) * C + c0 + c] = v;
+        });
+    if (with_bias)
+        put(accb, [&](int o, int c, float v) {
+            if (c == 0 && o0 + o < a.Cout) part[(size_t)a.Cout * 9 * C + o0 + o] = v;
+        });
 }
 
-// out[i] = sum_s part[s][i] (+ out[i] if accumulate).  A block takes 64 consecutive i;
-// its 4 rows of lanes take every 4th split, each with four independent partial sums
-// (splits k, k+4, k+8, k+12 of a stride of 16) so that several loads are in flight;
-// every combination is in a fixed order, so the result does not depend on scheduling.
-__global__ void __launch_bounds__(256) k_reduce_splits(const float* __restrict__ part, int nsplit,
-                                                       size_t n, float* __restrict__ out,
-                                                       int accumulate) {
-    __shared__ float sred[4][65];
+// Sum over the splits: sum_s part[s][i], i < n, rows of `stride`, into out[i] for i < nhead
+// and tail[i - nhead] from there on.  A block takes 64 consecutive i; its 16 rows of lanes
+// take every 16th split, each with four independent partial sums (in float64: the adds are
+// free beside the loads) so that several loads are in flight; every combination is in a
+// fixed order, so the result does not depend on scheduling.  (With 4 rows of lanes a
+// level-0 layer's 512 splits were a chain of 32 waits.)
+constexpr int RS_ROWS = 16;
+__global__ void __launch_bounds__(64 * RS_ROWS)
+k_reduce_splits(const float* __restrict__ part, int nsplit, size_t stride, size_t n, size_t nhead,
+                float* __restrict__ out, float* __restrict__ tail) {
+    __shared__ double sred[RS_ROWS][64];
     const int ci = threadIdx.x & 63, sl = threadIdx.x >> 6;
     const size_t i = (size_t)blockIdx.x * 64 + ci;
-    float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
     if (i < n) {
         int k = sl;
-        for (; k + 12 < nsplit; k += 16) {
-            a0 += part[(size_t)k * n + i];
-            a1 += part[(size_t)(k + 4) * n + i];
-            a2 += part[(size_t)(k + 8) * n + i];
-            a3 += part[(size_t)(k + 12) * n + i];
-        }
-        for (; k < nsplit; k += 4) a0 += part[(size_t)k * n + i];
+        for (; k + 3 * RS_ROWS < nsplit; k += 4 * RS_ROWS)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) s[u] += part[(size_t)(k + u * RS_ROWS) * stride + i];
+        for (; k < nsplit; k += RS_ROWS) s[0] += part[(size_t)k * stride + i];
     }
-    sred[sl][ci] = (a0 + a1) + (a2 + a3);
+    sred[sl][ci] = (s[0] + s[1]) + (s[2] + s[3]);
     __syncthreads();
     if (sl == 0 && i < n) {
-        const float t = ((sred[0][ci] + sred[1][ci]) + sred[2][ci]) + sred[3][ci];
-        out[i] = accumulate ? out[i] + t : t;
+        double t = sred[0][ci];
+#pragma unroll
+        for (int r = 1; r < RS_ROWS; ++r) t += sred[r][ci];
+        if (i < nhead) out[i] = (float)t;
+        else tail[i - nhead] = (float)t;
     }
 }
 
-// column sums of a [P][C] BF16 matrix over a pixel range per block: part[blk][C]
-__global__ void __launch_bounds__(256) k_colsum(const __bf16* __restrict__ m, int P, int C,
-                                                int px_per_block, float* __restrict__ part) {
-    __shared__ float s[256];
-    const int c = threadIdx.x % 32 + 32 * blockIdx.y;
-    const int r = threadIdx.x / 32;                   // 8 row lanes
-    const int pb = blockIdx.x * px_per_block, pe = min(P, pb + px_per_block);
-    float acc = 0.f;
-    if (c < C)
-        for (int p = pb + r; p < pe; p += 8) acc += (float)m[(size_t)p * C + c];
-    s[threadIdx.x] = acc;
-    __syncthreads();
-    if (r == 0 && c < C) {
-        float t = 0.f;
-        for (int k = 0; k < 8; ++k) t += s[k * 32 + threadIdx.x % 32];
-        part[(size_t)blockIdx.x * C + c] = t;
-    }
-}
-
-// dz[p, c] = d_act[p, c0 + c] * silu'(z[p, c]) (BF16), and per block of ppb pixels the
-// column sums of dz: part[block][c] (the bias gradient's partial sums)
+// dz[p, c] = d_act[p, c0 + c] * silu'(z[p, c]) (BF16), 8 channels a thread
 __global__ void __launch_bounds__(256) k_silu_bwd(const float* __restrict__ dact, int cs, int c0,
-                                                  const __bf16* __restrict__ z, int P, int C,
-                                                  int ppb, __bf16* __restrict__ dz,
-                                                  float* __restrict__ part) {
-    __shared__ float sred[8][33];
-    const int cl = threadIdx.x & 31, r = threadIdx.x >> 5;
-    const int c = blockIdx.y * 32 + cl;
-    const int pb = blockIdx.x * ppb, pe = min(P, pb + ppb);
-    float acc = 0.f;
-    if (c < C)
-#pragma unroll 8
-        for (int p = pb + r; p < pe; p += 8) {
-            const size_t i = (size_t)p * C + c;
-            const __bf16 d = (__bf16)(dact[(size_t)p * cs + c0 + c] * silu_grad((float)z[i]));
-            dz[i] = d;
-            acc += (float)d;
-        }
-    sred[r][cl] = acc;
-    __syncthreads();
-    if (r == 0 && c < C) {
-        float t = 0.f;
-        for (int k = 0; k < 8; ++k) t += sred[k][cl];
-        part[(size_t)blockIdx.x * C + c] = t;
-    }
+                                                  const __bf16* __restrict__ z, uint32_t n8, int C8,
+                                                  __bf16* __restrict__ dz) {
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    if (i >= n8) return;
+    const uint32_t p = i / (uint32_t)C8, c = (i - p * (uint32_t)C8) * 8;
+    const bf16x8 v = *reinterpret_cast<const bf16x8*>(z + (size_t)i * 8);
+    const float4* d = reinterpret_cast<const float4*>(dact + (size_t)p * cs + c0 + c);
+    const float4 d0 = d[0], d1 = d[1];
+    const float f[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
+    bf16x8 o;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = (__bf16)(f[e] * silu_grad((float)v[e]));
+    *reinterpret_cast<bf16x8*>(dz + (size_t)i * 8) = o;
 }
 
 // grad_hi[b, 2y+i, 2x+j, c0 + c] += dx_lo[b, y, x, c] / 4   (average pooling adjoint)
@@ -1360,37 +1447,41 @@ int wgrad_nsplit(int B, int H, int W, int Cout, int Cin, int* per_split) {
     return (np + per - 1) / per;
 }
 
-hipError_t wgrad(const WgradP& a, hipStream_t st) {
+size_t wgrad_part_floats(int B, int H, int W, int Cout, int Cin) {
+    int per;
+    return (size_t)wgrad_nsplit(B, H, W, Cout, Cin, &per) * ((size_t)Cout * 9 * Cin + Cout);
+}
+
+hipError_t wgrad(const WgradP& a, float* dw, float* db, hipStream_t st) {
     int per;
     const int ns = wgrad_nsplit(a.B, a.H, a.W, a.Cout, a.g.C, &per);
     const int np = wgrad_patches(a.B, a.H, a.W);
-    const dim3 grid((a.Cout + 31) / 32, (a.g.C + 31) / 32, ns);
+    const int npair = ((a.Cout + 31) / 32) * ((a.g.C + 31) / 32);
+    const dim3 grid(npair * ((ns + 7) / 8) * 8);
     if (a.g.mode == MODE_POOL)
-        hipLaunchKernelGGL((k_wgrad_tiled<MODE_POOL>), grid, dim3(256), 0, st, a, per, np);
+        hipLaunchKernelGGL((k_wgrad_tiled<MODE_POOL>), grid, dim3(256), 0, st, a, per, np, ns);
     else if (a.g.mode == MODE_UP)
-        hipLaunchKernelGGL((k_wgrad_tiled<MODE_UP>), grid, dim3(256), 0, st, a, per, np);
+        hipLaunchKernelGGL((k_wgrad_tiled<MODE_UP>), grid, dim3(256), 0, st, a, per, np, ns);
     else
-        hipLaunchKernelGGL((k_wgrad_tiled<MODE_SAME>), grid, dim3(256), 0, st, a, per, np);
+        hipLaunchKernelGGL((k_wgrad_tiled<MODE_SAME>), grid, dim3(256), 0, st, a, per, np, ns);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const size_t nw = (size_t)a.Cout * 9 * a.g.C;
+    return reduce_splits(a.part, ns, nw + a.Cout, db ? nw + a.Cout : nw, nw, dw, db, st);
+}
+
+hipError_t reduce_splits(const float* part, int nsplit, size_t stride, size_t n, size_t nhead,
+                         float* out, float* tail, hipStream_t st) {
+    hipLaunchKernelGGL(k_reduce_splits, dim3((unsigned)((n + 63) / 64)), dim3(64 * RS_ROWS), 0, st,
+                       part, nsplit, stride, n, nhead, out, tail);
     return hipGetLastError();
 }
 
-hipError_t reduce_splits(const float* part, int nsplit, size_t n, float* out, int acc,
-                         hipStream_t st) {
-    hipLaunchKernelGGL(k_reduce_splits, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, st, part,
-                       nsplit, n, out, acc);
-    return hipGetLastError();
-}
-
-hipError_t colsum(const __bf16* m, int P, int C, int px_per_block, float* part, hipStream_t st) {
-    hipLaunchKernelGGL(k_colsum, dim3((P + px_per_block - 1) / px_per_block, (C + 31) / 32),
-                       dim3(256), 0, st, m, P, C, px_per_block, part);
-    return hipGetLastError();
-}
-
-hipError_t silu_bwd(const float* dact, int cs, int c0, const __bf16* z, int P, int C, int ppb,
-                    __bf16* dz, float* part, hipStream_t st) {
-    hipLaunchKernelGGL(k_silu_bwd, dim3((P + ppb - 1) / ppb, (C + 31) / 32), dim3(256), 0, st, dact,
-                       cs, c0, z, P, C, ppb, dz, part);
+hipError_t silu_bwd(const float* dact, int cs, int c0, const __bf16* z, int P, int C, __bf16* dz,
+                    hipStream_t st) {
+    const size_t n8 = (size_t)P * C / 8;
+    hipLaunchKernelGGL(k_silu_bwd, dim3(blocks(n8)), dim3(256), 0, st, dact, cs, c0, z,
+                       (uint32_t)n8, C / 8, dz);
     return hipGetLastError();
 }
 
