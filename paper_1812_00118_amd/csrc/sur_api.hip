@@ -21,18 +21,17 @@ namespace {
 // Skip connections share a buffer with the decoder branch they are concatenated with,
 // so the concatenation is a channel offset.  POOLk holds the 2x2 averages of an encoder
 // output, written by the producing layer's epilogue and read by the next level's pooling
-// layer (no gradient buffer: the backward distributes through the pooling explicitly).
+// layer.
 enum Buf {
     X, E0A, CAT0, D0A, D0B, E1A, CAT1, D1A, D1B, E2A, CAT2, D2A, D2B, B3A, B3B,
     POOL0, POOL1, POOL2, NBUFS
 };
 struct BufDef {
-    int level, C, grad;
+    int level, C;
 };
-constexpr BufDef BUFS[NBUFS] = {{0, 8, 1},   {0, 32, 1},  {0, 64, 1},  {0, 32, 1},  {0, 32, 1},
-                            {1, 64, 1},  {1, 128, 1}, {1, 64, 1},  {1, 64, 1},  {2, 128, 1},
-                            {2, 256, 1}, {2, 128, 1}, {2, 128, 1}, {3, 256, 1}, {3, 256, 1},
-                            {1, 32, 0},  {2, 64, 0},  {3, 128, 0}};
+constexpr BufDef BUFS[NBUFS] = {{0, 8},   {0, 32},  {0, 64},  {0, 32},  {0, 32},  {1, 64},
+                            {1, 128}, {1, 64},  {1, 64},  {2, 128}, {2, 256}, {2, 128},
+                            {2, 128}, {3, 256}, {3, 256}, {1, 32},  {2, 64},  {3, 128}};
 
 // 3x3 layers in network order; level = output resolution.  pool_out: the buffer that also
 // receives the 2x2 average of this layer's output (channels 0..Cout); pool_in: a pooling
@@ -87,7 +86,7 @@ constexpr bool pool_links_ok() {
                 return false;
         }
         if (writers != 1 || R.mode != MODE_POOL || BUFS[R.pool_in].C != R.Cin ||
-            BUFS[R.pool_in].level != R.level || BUFS[R.pool_in].grad)
+            BUFS[R.pool_in].level != R.level)
             return false;
     }
     return true;
@@ -112,10 +111,28 @@ const ParamLayout PL;
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// byte offsets into the caller's workspace
+// The layer whose output is the last part of layer l's input, the first part being a skip
+// connection's where `skip` is set: the one before it, as the network is a chain.  For a
+// pooling layer the whole input is the skip connection's.
+constexpr bool chain_ok() {
+    for (int l = 1; l < NL; ++l) {
+        const LayerDef &A = LAYERS[l - 1], &R = LAYERS[l];
+        if (A.out_buf != R.in_buf || A.Cout + A.out_c0 != R.in_c0 + R.Cin) return false;
+        if (R.mode == MODE_SAME ? A.level != R.level || R.in_c0 != 0
+                                : R.in_c0 != A.out_c0 ||
+                                      A.level != R.level + (R.mode == MODE_UP ? 1 : -1))
+            return false;
+        if (R.mode == MODE_SAME && A.out_c0 != 0 && A.out_c0 * 2 != R.Cin) return false;
+    }
+    return true;
+}
+static_assert(chain_ok(), "the backward pass takes the layers as a chain");
+
+// byte offsets into the caller's workspace; skip: FP32 gradients of the skip connections'
+// halves of CAT0, CAT1, CAT2
 struct Plan {
-    size_t act[NBUFS], z[NL], dact[NBUFS];
-    size_t out, dout, dz, dx, part, mse_part, loss;
+    size_t act[NBUFS], z[NL], skip[NBUFS];
+    size_t dz[2], part, err, loss;
     size_t total;
 };
 
@@ -132,22 +149,16 @@ Plan make_plan(int H, int W, int B, bool training) {
     for (int k = 1; k < NBUFS; ++k) p.act[k] = take(pix(BUFS[k].level) * BUFS[k].C * 2);
     if (training) {
         for (int l = 0; l < NL; ++l) p.z[l] = take(pix(LAYERS[l].level) * LAYERS[l].Cout * 2);
-        for (int k = 1; k < NBUFS; ++k)
-            if (BUFS[k].grad) p.dact[k] = take(pix(BUFS[k].level) * BUFS[k].C * 4);
-        p.out = take(pix(0) * PFSUR_OUT_CH * 4);
-        p.dout = take(pix(0) * PFSUR_OUT_CH * 4);
-        size_t dz = 0, dx = 0, part = (size_t)head_blocks(pix(0)) * 132;
+        for (int k : {CAT0, CAT1, CAT2}) p.skip[k] = take(pix(BUFS[k].level) * (BUFS[k].C / 2) * 4);
+        size_t dz = 0, part = (size_t)head_blocks(pix(0)) * 132;
         for (int l = 0; l < NL; ++l) {
             const LayerDef& L = LAYERS[l];
-            const size_t P = pix(L.level);
-            dz = std::max(dz, P * L.Cout);
-            if (L.mode != MODE_SAME) dx = std::max(dx, P * L.Cin);
+            dz = std::max(dz, pix(L.level) * L.Cout);
             part = std::max(part, wgrad_part_floats(B, H >> L.level, W >> L.level, L.Cout, L.Cin));
         }
-        p.dz = take(dz * 2);
-        p.dx = take(dx * 4);
+        for (size_t& d : p.dz) d = take(dz * 2);
         p.part = take(part * 4);
-        p.mse_part = take((size_t)mse_blocks(pix(0) * PFSUR_OUT_CH) * 8);
+        p.err = take((size_t)head_blocks(pix(0)) * 8);
         p.loss = take(8);
     }
     p.total = o;
@@ -239,6 +250,7 @@ int run_forward(pfsur_ctx* c, const void* x, float* out, int B, char* ws, bool t
         const LayerDef& L = LAYERS[l];
         ConvP a;
         memset(&a, 0, sizeof(a));
+        a.bwd = -1;
         a.g = gather_of(L, ws, p, x, H, W);
         a.B = B;
         a.H = H >> L.level;
@@ -272,13 +284,6 @@ int run_forward(pfsur_ctx* c, const void* x, float* out, int B, char* ws, bool t
         else
             SUR_TRY(conv3x3(a, st), "conv forward");
     }
-    if (training) {
-        const size_t P0 = (size_t)B * H * W;
-        SUR_TRY(head_fwd(reinterpret_cast<const __bf16*>(ws + p.act[D0B]), HEAD_C, 0,
-                         c->master + PL.head, c->master + PL.head + PFSUR_OUT_CH * HEAD_C, P0,
-                         out, st),
-                "head forward");
-    }
     return PFLB_OK;
 }
 
@@ -287,41 +292,37 @@ int run_backward(pfsur_ctx* c, const void* x, const float* y, int B, char* ws, h
     const int H = c->cfg.H, W = c->cfg.W;
     const Plan p = make_plan(H, W, B, true);
     const size_t P0 = (size_t)B * H * W;
-    float* out = reinterpret_cast<float*>(ws + p.out);
-    float* dout = reinterpret_cast<float*>(ws + p.dout);
     float* part = reinterpret_cast<float*>(ws + p.part);
-    __bf16* dz = reinterpret_cast<__bf16*>(ws + p.dz);
-    float* dx = reinterpret_cast<float*>(ws + p.dx);
-    auto dact = [&](int buf) { return reinterpret_cast<float*>(ws + p.dact[buf]); };
-    SUR_TRY(mse(out, y, P0 * PFSUR_OUT_CH, dout, reinterpret_cast<double*>(ws + p.mse_part),
-                reinterpret_cast<double*>(ws + p.loss), st),
-            "mse");
-    SUR_TRY(head_bwd(reinterpret_cast<const __bf16*>(ws + p.act[D0B]), HEAD_C, 0,
-                     c->master + PL.head, dout, P0, dact(D0B), HEAD_C, 0, part, st),
-            "head backward");
+    auto zof = [&](int l) { return reinterpret_cast<const __bf16*>(ws + p.z[l]); };
+    // the dz of layer l, in the buffer that the dz of layer l + 1 leaves free
+    auto dzof = [&](int l) { return reinterpret_cast<__bf16*>(ws + p.dz[l & 1]); };
+    const float* wh = c->master + PL.head;
+    SUR_TRY(head_train(reinterpret_cast<const __bf16*>(ws + p.act[D0B]), wh,
+                       wh + PFSUR_OUT_CH * HEAD_C, y, zof(NL - 1), P0, dzof(NL - 1), part,
+                       reinterpret_cast<double*>(ws + p.err),
+                       reinterpret_cast<double*>(ws + p.loss), st),
+            "head");
     constexpr size_t nh = PFSUR_OUT_CH * (HEAD_C + 1);
     SUR_TRY(reduce_splits(part, (int)head_blocks(P0), nh, nh, nh, c->grad + PL.head, nullptr, st),
             "head reduce");
     for (int l = NL - 1; l >= 0; --l) {
         const LayerDef& L = LAYERS[l];
         const int Hl = H >> L.level, Wl = W >> L.level;
-        const int P = B * Hl * Wl;
-        SUR_TRY(silu_bwd(dact(L.out_buf), BUFS[L.out_buf].C, L.out_c0,
-                         reinterpret_cast<const __bf16*>(ws + p.z[l]), P, L.Cout, dz, st),
-                "silu backward");
         WgradP wg;
         wg.g = gather_of(L, ws, p, x, H, W);
         wg.B = B;
         wg.H = Hl;
         wg.W = Wl;
-        wg.dz = dz;
+        wg.dz = dzof(l);
         wg.Cout = L.Cout;
         wg.part = part;
         SUR_TRY(wgrad(wg, c->grad + PL.w[l], c->grad + PL.b[l], st), "wgrad");
         if (l == 0) continue;
+        // the input gradient, into the dz of the layer before (and the skip connection's half)
+        const LayerDef& A = LAYERS[l - 1];
         ConvP d;
         memset(&d, 0, sizeof(d));
-        d.g.p = dz;
+        d.g.p = dzof(l);
         d.g.Hin = Hl;
         d.g.Win = Wl;
         d.g.cs = L.Cout;
@@ -333,23 +334,16 @@ int run_backward(pfsur_ctx* c, const void* x, const float* y, int B, char* ws, h
         d.W = Wl;
         d.w = c->wt[l];
         d.Cout = L.Cin;
-        if (L.mode == MODE_SAME) {
-            d.fout = dact(L.in_buf);
-            d.f_cs = BUFS[L.in_buf].C;
-            d.f_c0 = L.in_c0;
-        } else {
-            d.fout = dx;
-            d.f_cs = L.Cin;
-            d.f_c0 = 0;
+        d.bwd = L.mode == MODE_UP ? BWD_UP : (L.mode == MODE_POOL ? BWD_POOL : BWD_SAME);
+        d.zin = zof(l - 1);
+        d.dz = dzof(l - 1);
+        d.dz_cs = A.Cout;
+        d.dz_c0 = L.mode == MODE_SAME ? A.out_c0 : 0;
+        if (L.mode == MODE_POOL || d.dz_c0) {
+            d.fout = reinterpret_cast<float*>(ws + p.skip[L.in_buf]);
+            d.f_cs = BUFS[L.in_buf].C / 2;
         }
         SUR_TRY(conv3x3(d, st), "dgrad");
-        if (L.mode == MODE_POOL)
-            SUR_TRY(unpool_add(dx, B, Hl, Wl, L.Cin, dact(L.in_buf), BUFS[L.in_buf].C, L.in_c0, st),
-                    "unpool");
-        else if (L.mode == MODE_UP)
-            SUR_TRY(sumpool(dx, B, Hl / 2, Wl / 2, L.Cin, dact(L.in_buf), BUFS[L.in_buf].C, L.in_c0,
-                            0, st),
-                    "sumpool");
     }
     return PFLB_OK;
 }
@@ -388,7 +382,7 @@ DensTab dens_tab(const double* rho, int b0, int nb) {
 int forward_backward(pfsur_ctx* c, const void* x, const float* y, int batch, float* loss,
                      char* ws, hipStream_t st) {
     const Plan p = make_plan(c->cfg.H, c->cfg.W, batch, true);
-    int r = run_forward(c, x, reinterpret_cast<float*>(ws + p.out), batch, ws, true, st);
+    int r = run_forward(c, x, nullptr, batch, ws, true, st);
     if (r) return r;
     r = run_backward(c, x, y, batch, ws, st);
     if (r) return r;
@@ -927,6 +921,7 @@ int pfsur_conv_fwd(const void* x, int batch, int H, int W, int Cin, int Cout, in
     if (!aligned16(x) || !aligned16(w)) return PFLB_ERR_ALIGN;
     ConvP a;
     memset(&a, 0, sizeof(a));
+    a.bwd = -1;
     a.g = plain_gather(x, H, W, Cin, mode);
     a.B = batch;
     a.H = H;

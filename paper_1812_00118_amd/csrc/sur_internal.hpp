@@ -24,7 +24,11 @@ struct GatherP {
 // pout (BF16 [B][H/2][W/2][pout_cs], channels from 0; needs out and even H, W) <- the 2x2
 // average of what out receives, as the pooling gather computes it.  head_out (FP32
 // [P][4]; 32-channel same-resolution layers only) <- the 1x1 head (head_w [4][32],
-// head_b [4]) applied to the BF16-rounded activations, as head_fwd computes it.
+// head_b [4]) applied to the BF16-rounded activations, as in training.
+// bwd >= 0 (input gradients; -1 elsewhere): the output is a gradient of activations, and what
+// is stored is dz = (that gradient) silu'(zin) of the layer that produced them, BF16 at
+// channel stride dz_cs, of the output channels from dz_c0 on (see tile_epilogue_bwd).
+enum { BWD_SAME = 0, BWD_UP = 1, BWD_POOL = 2 };
 struct ConvP {
     GatherP g;
     int B, H, W;
@@ -42,6 +46,10 @@ struct ConvP {
     const float* head_w;
     const float* head_b;
     float* head_out;
+    int bwd;
+    const __bf16* zin;
+    __bf16* dz;
+    int dz_cs, dz_c0;
 };
 
 // sums over pixels of dz[p, co] in[p + off(tap), ci] and of dz[p, co]; part: wgrad_part_floats
@@ -78,20 +86,12 @@ size_t wgrad_part_floats(int B, int H, int W, int Cout, int Cin);
 // tail[i - nhead]
 hipError_t reduce_splits(const float* part, int nsplit, size_t stride, size_t n, size_t nhead,
                          float* out, float* tail, hipStream_t st);
-hipError_t silu_bwd(const float* dact, int cs, int c0, const __bf16* z, int P, int C, __bf16* dz,
-                    hipStream_t st);
-hipError_t unpool_add(const float* dlo, int B, int Hl, int Wl, int C, float* ghi, int cs, int c0,
-                      hipStream_t st);
-hipError_t sumpool(const float* dhi, int B, int Hl, int Wl, int C, float* glo, int cs, int c0,
-                   int acc, hipStream_t st);
-hipError_t head_fwd(const __bf16* act, int cs, int c0, const float* wh, const float* bh, size_t P,
-                    float* out, hipStream_t st);
-hipError_t head_bwd(const __bf16* act, int cs, int c0, const float* wh, const float* dout, size_t P,
-                    float* dact, int dcs, int dc0, float* part, hipStream_t st);
+// the head's loss (sum of squared errors), its weight gradient's partial sums (part, 132 per
+// block, then 4) and the last layer's dz; err: a double per block of head_blocks
+hipError_t head_train(const __bf16* act, const float* wh, const float* bh, const float* y,
+                      const __bf16* z, size_t P, __bf16* dz, float* part, double* err,
+                      double* loss, hipStream_t st);
 unsigned head_blocks(size_t P);
-hipError_t mse(const float* out, const float* y, size_t n, float* dout, double* part, double* res,
-               hipStream_t st);
-unsigned mse_blocks(size_t n);
 hipError_t adam(float* w, const float* g, float* m, float* v, size_t n, float lr, int t,
                 hipStream_t st);
 hipError_t weights_bf16(const float* w, int Cout, int Cin, __bf16* wf, __bf16* wt, hipStream_t st);

@@ -380,9 +380,113 @@ __device__ __forceinline__ void tile_epilogue_staged(const ConvP& a, const f32x1
     }
 }
 
+// Epilogues of the backward pass: a layer's input gradient goes straight into the dz of the
+// layer that produced the input, dz = (gradient of its activation) silu'(z), rounded to BF16
+// once, so that the FP32 gradients (4 and more bytes a value, written and read again) stay
+// in registers.  Each gradient is formed as by separate passes, in the same order.
+//   BWD_SAME  the producer is at the same resolution.  Channels below a.dz_c0 belong to a
+//             skip connection, whose gradient gets a second part later: stored to a.fout.
+//   BWD_UP    the input was upsampled: the 2x2 sum of the gradient, at half resolution.
+//   BWD_POOL  the input was pooled: a quarter of the gradient on each of four pixels at
+//             double resolution, added to the skip connection's in a.fout.
+// (Gradients of 16 samples of 256x256: 725 us of element-wise kernels before, none now.)
+__device__ __forceinline__ void silu_bwd(float (&v)[16], const __bf16* z, int g) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const bf16x4 zq = *reinterpret_cast<const bf16x4*>(z + 8 * q + 4 * g);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[4 * q + e] *= silu_grad((float)zq[e]);
+    }
+}
+
+template <int NB, int BWD>
+__device__ __forceinline__ void tile_epilogue_bwd(const ConvP& a, const f32x16 (&acc)[2][NB],
+                                                  int b, int y0, int x0, int co0, int wave,
+                                                  int l32, int g, __bf16* __restrict__ sO) {
+    const int lane = l32 + 32 * g;
+    __bf16* so = sO + wave * 64 * OROW;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        const int cb = co0 + nb * 32, cd = cb - a.dz_c0;   // channel of the tile, of dz
+        if (cb >= a.Cout) break;
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb) {
+            const int y = y0 + 4 * wave + 2 * mb + (l32 >> 4), x = x0 + (l32 & 15);
+            const bool in = y < a.H && x < a.W;
+            const size_t p = ((size_t)b * a.H + y) * a.W + x;
+            float v[16];
+            bf16x4 o[4];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) v[e] = acc[mb][nb][e];
+            if constexpr (BWD == BWD_SAME) {
+                if (cd < 0) {
+                    if (in) put_f32(a, p, cb, g, v);
+                    continue;
+                }
+                if (in) silu_bwd(v, a.zin + p * a.dz_cs + cd, g);
+                to_bf16(v, 0, o);
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<bf16x4*>(&so[(mb * 32 + l32) * OROW + 8 * q + 4 * g]) = o[q];
+            } else if constexpr (BWD == BWD_UP) {
+                // lanes l, l^1, l^16, l^17 hold the 2x2 block
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const float r = __shfl_xor(v[e], 1);
+                    v[e] = ((v[e] + r) + __shfl_xor(v[e], 16)) + __shfl_xor(r, 16);
+                }
+                if (in && !(y & 1) && !(x & 1)) {
+                    const size_t pl = ((size_t)b * (a.H >> 1) + (y >> 1)) * (a.W >> 1) + (x >> 1);
+                    silu_bwd(v, a.zin + pl * a.dz_cs + cd, g);
+                    to_bf16(v, 0, o);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        *reinterpret_cast<bf16x4*>(a.dz + pl * a.dz_cs + cd + 8 * q + 4 * g) = o[q];
+                }
+            } else {
+                if (!in) continue;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const size_t ph = ((size_t)b * 2 * a.H + 2 * y + (k >> 1)) * 2 * a.W + 2 * x + (k & 1);
+                    const float* sk = a.fout + ph * a.f_cs + a.f_c0 + cb + 4 * g;
+                    float t[16];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float4 f = *reinterpret_cast<const float4*>(sk + 8 * q);
+                        t[4 * q] = fmaf(0.25f, v[4 * q], f.x);
+                        t[4 * q + 1] = fmaf(0.25f, v[4 * q + 1], f.y);
+                        t[4 * q + 2] = fmaf(0.25f, v[4 * q + 2], f.z);
+                        t[4 * q + 3] = fmaf(0.25f, v[4 * q + 3], f.w);
+                    }
+                    silu_bwd(t, a.zin + ph * a.dz_cs + cd, g);
+                    to_bf16(t, 0, o);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        *reinterpret_cast<bf16x4*>(a.dz + ph * a.dz_cs + cd + 8 * q + 4 * g) = o[q];
+                }
+            }
+        }
+        if constexpr (BWD == BWD_SAME) {
+            if (cd < 0) continue;
+            wave_lds_sync();
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int px = (lane >> 2) + 16 * k, grp = lane & 3;
+                const int pl = px & 31;
+                const int y = y0 + 4 * wave + 2 * (px >> 5) + (pl >> 4), x = x0 + (pl & 15);
+                const bf16x8 val = *reinterpret_cast<const bf16x8*>(&so[px * OROW + 8 * grp]);
+                if (y < a.H && x < a.W)
+                    *reinterpret_cast<bf16x8*>(
+                        a.dz + (((size_t)b * a.H + y) * a.W + x) * a.dz_cs + cd + 8 * grp) = val;
+            }
+            wave_lds_sync();
+        }
+    }
+}
+
 // Partial sums of the 1x1 head over the 16 channels 8q + 4g + e (q, e = 0..3) of one
 // pixel, in that order.  A head output is (half(g = 0) + half(g = 1)) + b: the order
-// head_fwd uses and the one the fused epilogue gets, where lanes l and l + 32 of a wave
+// k_head_train uses and the one the fused epilogue gets, where lanes l and l + 32 of a wave
 // hold the two halves of a pixel's 32 channels.
 __device__ __forceinline__ void head_half(const float (&v)[16], int g, const float* wh,
                                           float (&p)[4]) {
@@ -429,10 +533,11 @@ __device__ __forceinline__ void tile_epilogue_head(const ConvP& a, const f32x16 
 // registers allow it; 64-channel tiles (69 KB) fit two, and so does the fused-head variant, whose
 // head arithmetic needs the registers of two workgroups per CU.
 // Epilogue variants: staged (always for 64-channel tiles; for 32-channel tiles only when
-// the layer also writes pooled output), direct, or the fused 1x1 head.
-enum { EPI_DIRECT = 0, EPI_STAGED = 1, EPI_HEAD = 2 };
+// the layer also writes pooled output), direct, the fused 1x1 head, or one of the backward
+// pass's.
+enum { EPI_DIRECT = 0, EPI_STAGED = 1, EPI_HEAD = 2, EPI_BWD = 3 };   // EPI_BWD + BWD_*
 template <int NT, int MODE, int EPI>
-__global__ void __launch_bounds__(256, (NT == 32 && EPI != EPI_HEAD) ? 3 : 2)
+__global__ void __launch_bounds__(256, (NT == 32 && EPI < EPI_HEAD) ? 3 : 2)
 k_conv_tiled(ConvP a, int tiles_per_wg) {
     constexpr int NB = NT / 32;
     __shared__ __align__(16) __bf16 sA[HP * ROWA];
@@ -597,6 +702,9 @@ k_conv_tiled(ConvP a, int tiles_per_wg) {
             if constexpr (EPI == EPI_STAGED) {
                 __syncthreads();                 // every wave is done reading the patch
                 tile_epilogue_staged<NB>(a, acc, b, y0, x0, co0, wave, l32, g, sBias, sA);
+            } else if constexpr (EPI >= EPI_BWD) {
+                if (EPI == EPI_BWD + BWD_SAME) __syncthreads();
+                tile_epilogue_bwd<NB, EPI - EPI_BWD>(a, acc, b, y0, x0, co0, wave, l32, g, sA);
             } else if constexpr (EPI == EPI_HEAD) {
                 tile_epilogue_head(a, acc, b, y0, x0, wave, l32, g, sBias, sH);
             } else {
@@ -1032,149 +1140,113 @@ k_reduce_splits(const float* __restrict__ part, int nsplit, size_t stride, size_
     }
 }
 
-// dz[p, c] = d_act[p, c0 + c] * silu'(z[p, c]) (BF16), 8 channels a thread
-__global__ void __launch_bounds__(256) k_silu_bwd(const float* __restrict__ dact, int cs, int c0,
-                                                  const __bf16* __restrict__ z, uint32_t n8, int C8,
-                                                  __bf16* __restrict__ dz) {
-    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
-    if (i >= n8) return;
-    const uint32_t p = i / (uint32_t)C8, c = (i - p * (uint32_t)C8) * 8;
-    const bf16x8 v = *reinterpret_cast<const bf16x8*>(z + (size_t)i * 8);
-    const float4* d = reinterpret_cast<const float4*>(dact + (size_t)p * cs + c0 + c);
-    const float4 d0 = d[0], d1 = d[1];
-    const float f[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
-    bf16x8 o;
+// The 1x1 head in training, forward and backward in one pass over the last layer's
+// activations, for HEAD_PPB pixels per block: out[p, o] = bh[o] + sum_c act[p, c] wh[o, c]
+// (the order of head_half, as at inference), the squared error against y, dout =
+// 2 (out - y) / n, the last layer's dz[p, c] = silu'(z[p, c]) sum_o dout[p, o] wh[o, c], and
+// the partial sums part[block][o * 32 + c] of dout[p, o] act[p, c], part[block][128 + o] of
+// dout[p, o] and err[block] of the squared error.  First a thread takes a pixel (out and
+// dout, kept in LDS), then a pair of channels of every 16th pixel, so that the 128 sums need
+// one reduction over 16 threads at the end (a thread per pixel for all of it spent 790
+// shuffles on them; with separate passes for out, dout and the rest: 115 us on 16x256x256).
+constexpr int HEAD_PPB = 1024;
+__global__ void __launch_bounds__(256) k_head_train(const __bf16* __restrict__ act,
+                                                    const float* __restrict__ wh,
+                                                    const float* __restrict__ bh,
+                                                    const float* __restrict__ y,
+                                                    const __bf16* __restrict__ z, size_t P,
+                                                    float scale, __bf16* __restrict__ dz,
+                                                    float* __restrict__ part,
+                                                    double* __restrict__ err) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    __shared__ float4 sd[256];
+    __shared__ double sred[16][136];
+    __shared__ double serr[256];
+    const int c = 2 * (threadIdx.x & 15), r = threadIdx.x >> 4;
+    float w[4][2];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = (__bf16)(f[e] * silu_grad((float)v[e]));
-    *reinterpret_cast<bf16x8*>(dz + (size_t)i * 8) = o;
-}
-
-// grad_hi[b, 2y+i, 2x+j, c0 + c] += dx_lo[b, y, x, c] / 4   (average pooling adjoint)
-__global__ void k_unpool_add(const float* __restrict__ dlo, int B, int Hl, int Wl, int C,
-                             float* __restrict__ ghi, int cs, int c0) {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    const size_t n = (size_t)B * 4 * Hl * Wl * C;
-    if (i >= n) return;
-    const int c = (int)(i % C);
-    size_t p = i / C;
-    const int x = (int)(p % (2 * Wl));
-    p /= 2 * Wl;
-    const int y = (int)(p % (2 * Hl));
-    const int b = (int)(p / (2 * Hl));
-    ghi[(((size_t)b * 2 * Hl + y) * 2 * Wl + x) * cs + c0 + c] +=
-        0.25f * dlo[(((size_t)b * Hl + y / 2) * Wl + x / 2) * C + c];
-}
-
-// grad_lo[b, y, x, c0 + c] (+)= sum_{i,j} dx_hi[b, 2y+i, 2x+j, c]   (upsampling adjoint)
-__global__ void k_sumpool(const float* __restrict__ dhi, int B, int Hl, int Wl, int C,
-                          float* __restrict__ glo, int cs, int c0, int acc) {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    const size_t n = (size_t)B * Hl * Wl * C;
-    if (i >= n) return;
-    const int c = (int)(i % C);
-    const size_t p = i / C;
-    const int x = (int)(p % Wl);
-    const int y = (int)((p / Wl) % Hl);
-    const int b = (int)(p / ((size_t)Wl * Hl));
-    float s = 0.f;
-    for (int a = 0; a < 2; ++a)
-        for (int bb = 0; bb < 2; ++bb)
-            s += dhi[(((size_t)b * 2 * Hl + 2 * y + a) * 2 * Wl + 2 * x + bb) * C + c];
-    float* g = glo + p * cs + c0 + c;
-    *g = acc ? *g + s : s;
-}
-
-// 1x1 head: out[p, o] = bh[o] + sum_c act[p, c] wh[o, c]   (32 -> 4)
-__global__ void k_head_fwd(const __bf16* __restrict__ act, int cs, int c0, const float* __restrict__ wh,
-                           const float* __restrict__ bh, size_t P, float* __restrict__ out) {
-    const size_t p = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (p >= P) return;
-    float v0[16], v1[16];
+    for (int o = 0; o < 4; ++o)
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            v0[4 * q + e] = (float)act[p * cs + c0 + 8 * q + e];
-            v1[4 * q + e] = (float)act[p * cs + c0 + 8 * q + 4 + e];
-        }
-    float p0[4], p1[4];
-    head_half(v0, 0, wh, p0);
-    head_half(v1, 1, wh, p1);
-    for (int k = 0; k < 4; ++k) out[p * 4 + k] = (p0[k] + p1[k]) + bh[k];
-}
-
-// head backward: dact[p, c] = sum_o dout[p, o] wh[o, c]; per block of HEAD_PPB pixels the
-// partial sums part[blk][o * 32 + c] of dwh[o, c] = sum_p dout[p, o] act[p, c] and
-// part[blk][128 + o] of dbh[o] = sum_p dout[p, o].  Each thread accumulates its pixels in
-// registers; waves reduce by butterfly shuffles, then the 4 wave sums are added in order.
-constexpr int HEAD_PPB = 2048;
-__global__ void __launch_bounds__(256) k_head_bwd(const __bf16* __restrict__ act, int cs, int c0,
-                                                  const float* __restrict__ wh,
-                                                  const float* __restrict__ dout, size_t P,
-                                                  float* __restrict__ dact, int dcs, int dc0,
-                                                  float* __restrict__ part) {
-    __shared__ float sred[4][132];
-    float acc[132];
-#pragma unroll
-    for (int k = 0; k < 132; ++k) acc[k] = 0.f;
+        for (int e = 0; e < 2; ++e) w[o][e] = wh[32 * o + c + e];
+    double dw[4][2] = {}, db = 0.0, e2 = 0.0;
     const size_t pb = (size_t)blockIdx.x * HEAD_PPB;
     const size_t pe = pb + HEAD_PPB < P ? pb + HEAD_PPB : P;
-    for (size_t p = pb + threadIdx.x; p < pe; p += 256) {
-        const float4 d4 = reinterpret_cast<const float4*>(dout)[p];
-        const float d[4] = {d4.x, d4.y, d4.z, d4.w};
+    for (size_t p0 = pb; p0 < pe; p0 += 256) {
+        const size_t p = p0 + threadIdx.x;
+        float4 d = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (p < pe) {
+            float v0[16], v1[16], h0[4], h1[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const bf16x8 v = *reinterpret_cast<const bf16x8*>(act + p * cs + c0 + 8 * q);
-            float g[8];
+            for (int q = 0; q < 4; ++q) {
+                const bf16x8 v = *reinterpret_cast<const bf16x8*>(act + p * 32 + 8 * q);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int c = 8 * q + e;
-                const float av = (float)v[e];
-                g[e] = d[0] * wh[c] + d[1] * wh[32 + c] + d[2] * wh[64 + c] + d[3] * wh[96 + c];
-#pragma unroll
-                for (int o = 0; o < 4; ++o) acc[o * 32 + c] += d[o] * av;
+                for (int e = 0; e < 4; ++e) {
+                    v0[4 * q + e] = (float)v[e];
+                    v1[4 * q + e] = (float)v[4 + e];
+                }
             }
-            float4* dst = reinterpret_cast<float4*>(dact + p * dcs + dc0 + 8 * q);
-            dst[0] = make_float4(g[0], g[1], g[2], g[3]);
-            dst[1] = make_float4(g[4], g[5], g[6], g[7]);
+            head_half(v0, 0, wh, h0);
+            head_half(v1, 1, wh, h1);
+            const float4 t = reinterpret_cast<const float4*>(y)[p];
+            d = make_float4(((h0[0] + h1[0]) + bh[0]) - t.x, ((h0[1] + h1[1]) + bh[1]) - t.y,
+                            ((h0[2] + h1[2]) + bh[2]) - t.z, ((h0[3] + h1[3]) + bh[3]) - t.w);
+            e2 += ((double)d.x * d.x + (double)d.y * d.y) + ((double)d.z * d.z + (double)d.w * d.w);
+            d = make_float4(2.0f * d.x / scale, 2.0f * d.y / scale, 2.0f * d.z / scale,
+                            2.0f * d.w / scale);
         }
+        __syncthreads();
+        sd[threadIdx.x] = d;
+        __syncthreads();
+        const int np = (int)(pe - p0 < 256 ? pe - p0 : 256);
 #pragma unroll
-        for (int o = 0; o < 4; ++o) acc[128 + o] += d[o];
+        for (int k0 = 0; k0 < 16; k0 += 8) {
+            float s[4][2] = {}, sb = 0.0f;
+#pragma unroll
+            for (int k = k0; k < k0 + 8; ++k) {
+                const int j = r + 16 * k;
+                if (j < np) {
+                    const float4 q = sd[j];
+                    const float dd[4] = {q.x, q.y, q.z, q.w};
+                    const bf16x2 av = *reinterpret_cast<const bf16x2*>(act + (p0 + j) * 32 + c);
+                    const bf16x2 zv = *reinterpret_cast<const bf16x2*>(z + (p0 + j) * 32 + c);
+                    bf16x2 ov;
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const float gr =
+                            fmaf(dd[3], w[3][e],
+                                 fmaf(dd[2], w[2][e], fmaf(dd[0], w[0][e], dd[1] * w[1][e])));
+#pragma unroll
+                        for (int o = 0; o < 4; ++o) s[o][e] = fmaf(dd[o], (float)av[e], s[o][e]);
+                        ov[e] = (__bf16)(gr * silu_grad((float)zv[e]));
+                    }
+                    *reinterpret_cast<bf16x2*>(dz + (p0 + j) * 32 + c) = ov;
+                    if (c < 8) sb += dd[c >> 1];
+                }
+            }
+#pragma unroll
+            for (int o = 0; o < 4; ++o)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) dw[o][e] += (double)s[o][e];
+            db += (double)sb;
+        }
     }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-    for (int k = 0; k < 132; ++k) {
-        float v = acc[k];
+    for (int o = 0; o < 4; ++o)
 #pragma unroll
-        for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m);
-        if (lane == 0) sred[wave][k] = v;
-    }
+        for (int e = 0; e < 2; ++e) sred[r][32 * o + c + e] = dw[o][e];
+    if (c < 8) sred[r][128 + (c >> 1)] = db;
+    serr[threadIdx.x] = e2;
     __syncthreads();
-    if (threadIdx.x < 132)
-        part[(size_t)blockIdx.x * 132 + threadIdx.x] =
-            ((sred[0][threadIdx.x] + sred[1][threadIdx.x]) + sred[2][threadIdx.x]) +
-            sred[3][threadIdx.x];
-}
-
-// MSE: per-block partial sums of (out - y)^2 and dout = 2 (out - y) / n
-__global__ void __launch_bounds__(256) k_mse(const float* __restrict__ out, const float* __restrict__ y,
-                                             size_t n, float* __restrict__ dout,
-                                             double* __restrict__ part) {
-    __shared__ double s[256];
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    double e = 0.0;
-    if (i < n) {
-        const float d = out[i] - y[i];
-        e = (double)d * d;
-        if (dout) dout[i] = 2.0f * d / (float)n;
+    if (threadIdx.x < 132) {
+        double t = 0.0;
+        for (int k = 0; k < 16; ++k) t += sred[k][threadIdx.x];
+        part[(size_t)blockIdx.x * 132 + threadIdx.x] = (float)t;
     }
-    s[threadIdx.x] = e;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < (unsigned)w) s[threadIdx.x] += s[threadIdx.x + w];
+    for (int n = 128; n > 0; n >>= 1) {
+        if (threadIdx.x < (unsigned)n) serr[threadIdx.x] += serr[threadIdx.x + n];
         __syncthreads();
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = s[0];
+    if (threadIdx.x == 0) err[blockIdx.x] = serr[0];
 }
 
 __global__ void __launch_bounds__(256) k_sum_f64(const double* __restrict__ part, int n,
@@ -1373,7 +1445,7 @@ static hipError_t launch_tiled(const ConvP& a, hipStream_t st) {
     // 64-channel tiles and the fused-head variant, as their launch bounds say); each walks
     // a contiguous run of tiles so that the loads of its next tile overlap the MFMAs of
     // the current one
-    const int resident = NT == 32 && !a.head_out ? 768 : 512;
+    const int resident = NT == 32 && !a.head_out && a.bwd < 0 ? 768 : 512;
     const int ntile = a.B * ((a.H + TP - 1) / TP) * ((a.W + TP - 1) / TP);
     const int nblk_n = (a.Cout + NT - 1) / NT;
     const int per = std::max(1, (ntile * nblk_n + resident - 1) / resident);
@@ -1381,6 +1453,23 @@ static hipError_t launch_tiled(const ConvP& a, hipStream_t st) {
     if (a.pout && (a.H % 2 || a.W % 2 || !a.out || (NT == 32 && a.g.mode != MODE_SAME)))
         return hipErrorInvalidValue;
     constexpr int E = NT == 64 ? EPI_STAGED : EPI_DIRECT;
+    if (a.bwd >= 0) {
+        if (a.g.mode != MODE_SAME || !a.zin || !a.dz || a.bias || a.zout || a.out || a.pout ||
+            a.head_out || a.dz_c0 % 32 || (a.bwd != BWD_SAME && a.dz_c0) ||
+            (a.bwd == BWD_POOL && !a.fout) || (a.dz_c0 && !a.fout) ||
+            (a.bwd == BWD_UP && (a.H % 2 || a.W % 2)))
+            return hipErrorInvalidValue;
+        if (a.bwd == BWD_SAME)
+            hipLaunchKernelGGL((k_conv_tiled<NT, MODE_SAME, EPI_BWD + BWD_SAME>), grid, dim3(256),
+                               0, st, a, per);
+        else if (a.bwd == BWD_UP)
+            hipLaunchKernelGGL((k_conv_tiled<NT, MODE_SAME, EPI_BWD + BWD_UP>), grid, dim3(256), 0,
+                               st, a, per);
+        else
+            hipLaunchKernelGGL((k_conv_tiled<NT, MODE_SAME, EPI_BWD + BWD_POOL>), grid, dim3(256),
+                               0, st, a, per);
+        return hipGetLastError();
+    }
     if (a.head_out) {
         if constexpr (NT == 32) {
             if (a.Cout != 32 || a.g.mode != MODE_SAME || a.out || a.zout || a.fout || a.pout ||
@@ -1420,14 +1509,14 @@ hipError_t conv_stem(const ConvP& a0, const ConvP& a, hipStream_t st) {
 
 hipError_t conv3x3(const ConvP& a, hipStream_t st) {
     if (a.g.C == 8 && a.g.mode == MODE_SAME && a.Cout % 32 == 0) {
-        if (a.pout || a.head_out) return hipErrorInvalidValue;
+        if (a.pout || a.head_out || a.bwd >= 0) return hipErrorInvalidValue;
         const dim3 grid(a.B * ((a.H + TP - 1) / TP) * ((a.W + TP - 1) / TP), a.Cout / 32);
         hipLaunchKernelGGL(k_conv_first, grid, dim3(256), 0, st, a);
         return hipGetLastError();
     }
     if (a.g.C % 32 == 0 && a.Cout % 32 == 0)
         return a.Cout % 64 == 0 ? launch_tiled<64>(a, st) : launch_tiled<32>(a, st);
-    if (a.pout || a.head_out) return hipErrorInvalidValue;   // only the tiled kernels fuse
+    if (a.pout || a.head_out || a.bwd >= 0) return hipErrorInvalidValue;   // only the tiled kernels fuse
     const int P = a.B * a.H * a.W;
     hipLaunchKernelGGL(k_conv3x3, dim3((P + 255) / 256, (a.Cout + 31) / 32), dim3(256), 0, st, a);
     return hipGetLastError();
@@ -1477,51 +1566,17 @@ hipError_t reduce_splits(const float* part, int nsplit, size_t stride, size_t n,
     return hipGetLastError();
 }
 
-hipError_t silu_bwd(const float* dact, int cs, int c0, const __bf16* z, int P, int C, __bf16* dz,
-                    hipStream_t st) {
-    const size_t n8 = (size_t)P * C / 8;
-    hipLaunchKernelGGL(k_silu_bwd, dim3(blocks(n8)), dim3(256), 0, st, dact, cs, c0, z,
-                       (uint32_t)n8, C / 8, dz);
-    return hipGetLastError();
-}
-
-hipError_t unpool_add(const float* dlo, int B, int Hl, int Wl, int C, float* ghi, int cs, int c0,
-                      hipStream_t st) {
-    hipLaunchKernelGGL(k_unpool_add, dim3(blocks((size_t)B * 4 * Hl * Wl * C)), dim3(256), 0, st,
-                       dlo, B, Hl, Wl, C, ghi, cs, c0);
-    return hipGetLastError();
-}
-
-hipError_t sumpool(const float* dhi, int B, int Hl, int Wl, int C, float* glo, int cs, int c0,
-                   int acc, hipStream_t st) {
-    hipLaunchKernelGGL(k_sumpool, dim3(blocks((size_t)B * Hl * Wl * C)), dim3(256), 0, st, dhi, B,
-                       Hl, Wl, C, glo, cs, c0, acc);
-    return hipGetLastError();
-}
-
-hipError_t head_fwd(const __bf16* act, int cs, int c0, const float* wh, const float* bh, size_t P,
-                    float* out, hipStream_t st) {
-    hipLaunchKernelGGL(k_head_fwd, dim3(blocks(P)), dim3(256), 0, st, act, cs, c0, wh, bh, P, out);
-    return hipGetLastError();
-}
-
-hipError_t head_bwd(const __bf16* act, int cs, int c0, const float* wh, const float* dout, size_t P,
-                    float* dact, int dcs, int dc0, float* part, hipStream_t st) {
-    hipLaunchKernelGGL(k_head_bwd, dim3(head_blocks(P)), dim3(256), 0, st, act, cs, c0, wh, dout, P, dact,
-                       dcs, dc0, part);
+hipError_t head_train(const __bf16* act, const float* wh, const float* bh, const float* y,
+                      const __bf16* z, size_t P, __bf16* dz, float* part, double* err,
+                      double* loss, hipStream_t st) {
+    const unsigned nb = head_blocks(P);
+    hipLaunchKernelGGL(k_head_train, dim3(nb), dim3(256), 0, st, act, wh, bh, y, z, P,
+                       (float)(P * 4), dz, part, err);
+    hipLaunchKernelGGL(k_sum_f64, dim3(1), dim3(256), 0, st, err, (int)nb, loss);
     return hipGetLastError();
 }
 
 unsigned head_blocks(size_t P) { return (unsigned)((P + HEAD_PPB - 1) / HEAD_PPB); }
-
-hipError_t mse(const float* out, const float* y, size_t n, float* dout, double* part, double* res,
-               hipStream_t st) {
-    hipLaunchKernelGGL(k_mse, dim3(blocks(n)), dim3(256), 0, st, out, y, n, dout, part);
-    hipLaunchKernelGGL(k_sum_f64, dim3(1), dim3(256), 0, st, part, (int)blocks(n), res);
-    return hipGetLastError();
-}
-
-unsigned mse_blocks(size_t n) { return blocks(n); }
 
 hipError_t adam(float* w, const float* g, float* m, float* v, size_t n, float lr, int t,
                 hipStream_t st) {
