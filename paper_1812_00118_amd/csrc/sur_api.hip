@@ -256,6 +256,7 @@ int run_forward(pfsur_ctx* c, const void* x, float* out, int B, char* ws, bool t
         a.H = H >> L.level;
         a.W = W >> L.level;
         a.w = c->wf[l];
+        a.packed = l > 0;
         a.Cout = L.Cout;
         a.bias = c->master + PL.b[l];
         a.act = 1;
@@ -333,6 +334,7 @@ int run_backward(pfsur_ctx* c, const void* x, const float* y, int B, char* ws, h
         d.H = Hl;
         d.W = Wl;
         d.w = c->wt[l];
+        d.packed = 1;
         d.Cout = L.Cin;
         d.bwd = L.mode == MODE_UP ? BWD_UP : (L.mode == MODE_POOL ? BWD_POOL : BWD_SAME);
         d.zin = zof(l - 1);

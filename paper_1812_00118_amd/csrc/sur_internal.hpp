@@ -18,7 +18,8 @@ struct GatherP {
     int mode;
 };
 
-// out[p, co] for p over B x H x W output pixels, co < Cout; weights [Cout][9][C] BF16.
+// out[p, co] for p over B x H x W output pixels, co < Cout; weights [Cout][9][C] BF16, or (packed)
+// in the order weights_bf16 lays them out in (C and Cout multiples of 32).
 // Epilogue: v = acc + bias; zout (BF16 [P][Cout]) <- v; out (BF16 at channel stride
 // out_cs, offset out_c0) <- act ? silu(v) : v; fout (FP32 at f_cs, f_c0) <- v;
 // pout (BF16 [B][H/2][W/2][pout_cs], channels from 0; needs out and even H, W) <- the 2x2
@@ -33,6 +34,7 @@ struct ConvP {
     GatherP g;
     int B, H, W;
     const __bf16* w;
+    int packed;
     int Cout;
     const float* bias;
     int act;

@@ -10,10 +10,19 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "sur_internal.hpp"
 
 namespace pfsur {
+
+template <int I, int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, N>(f);
+    }
+}
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -182,23 +191,13 @@ __global__ void __launch_bounds__(256) k_conv3x3(ConvP a) {
 }
 
 // ---------------------------------------------------------------------------
-// Implicit-GEMM 3x3 convolution staged through LDS, for C and Cout multiples of 32.
-// A workgroup (4 waves) computes a 16x16 patch of output pixels of one image x NT
-// output channels.  The input channels are processed in chunks of 32: the chunk's
-// 18x18 halo patch (wrap, pooling or upsampling applied while loading) and its
-// NT x 9 x 32 weights are staged in LDS, and the loads of the next chunk are issued
-// into registers before the current chunk is computed.  Wave w owns patch rows
-// 4w..4w+3 as two 32-pixel blocks; v_mfma_f32_32x32x16_bf16 takes the weights as A
-// (lane l: row l%32 = output channel, K elements 8(l/32)..+7) and the pixels as B
-// (column l%32 = pixel, same K), so D[channel][pixel] has lane l on pixel l%32 with
-// channels 8(j/4) + 4(l/32) + j%4.  Row strides are padded (40 and 296 BF16) so that 16
-// consecutive lanes reading 16 bytes hit distinct banks.
+// 16x16-pixel tiles of the first two layers (k_conv_first, k_conv_stem): wave w owns patch
+// rows 4w..4w+3 as two 32-pixel blocks of two rows.
 // ---------------------------------------------------------------------------
 constexpr int TP = 16;                 // output patch edge
 constexpr int HP = TP + 2;             // halo patch edge
 constexpr int UPH = TP / 2 + 2;        // the same at half resolution (an upsampled input)
 constexpr int APAD = 40;               // BF16 per staged pixel (32 channels + pad)
-constexpr int BPAD = 9 * 32 + 8;       // BF16 per staged output channel
 // Row pitch of the staged halo patch: HP pixels of APAD BF16 plus RPAD BF16, so that a
 // row is 112 16-byte units (16 mod 32).  The 32 lanes of a B-operand read cover two patch
 // rows of 16 pixels, and gfx950's LDS serves such a 16-byte read in 512-byte groups of
@@ -215,7 +214,7 @@ constexpr int ROWA = HP * APAD + RPAD; // BF16 per staged patch row
 //
 // The bias comes from LDS (sBias, the workgroup's output channels, zeros without a bias): as
 // per-lane loads from memory, each behind its own wait, it was the largest part of the
-// epilogue (see k_conv_tiled).
+// epilogue of the row kernel below.
 //
 // values of row block mb, channel block nb: 4 runs of 4 channels
 template <int NB, int MB>
@@ -380,106 +379,122 @@ __device__ __forceinline__ void tile_epilogue_staged(const ConvP& a, const f32x1
     }
 }
 
-// Epilogues of the backward pass: a layer's input gradient goes straight into the dz of the
-// layer that produced the input, dz = (gradient of its activation) silu'(z), rounded to BF16
-// once, so that the FP32 gradients (4 and more bytes a value, written and read again) stay
-// in registers.  Each gradient is formed as by separate passes, in the same order.
-//   BWD_SAME  the producer is at the same resolution.  Channels below a.dz_c0 belong to a
-//             skip connection, whose gradient gets a second part later: stored to a.fout.
-//   BWD_UP    the input was upsampled: the 2x2 sum of the gradient, at half resolution.
-//   BWD_POOL  the input was pooled: a quarter of the gradient on each of four pixels at
-//             double resolution, added to the skip connection's in a.fout.
-// (Gradients of 16 samples of 256x256: 725 us of element-wise kernels before, none now.)
-__device__ __forceinline__ void silu_bwd(float (&v)[16], const __bf16* z, int g) {
+// ---------------------------------------------------------------------------
+// Implicit-GEMM 3x3 convolution for C and Cout multiples of 32.  A workgroup (4 waves)
+// computes NCB blocks of 32 output channels x ROWS rows of 32 output pixels of one image;
+// a wave one block x RW rows, on v_mfma_f32_32x32x16_bf16 with the weights as A (lane l: row
+// l%32 = output channel, K elements 8(l/32)..+7) and a row of pixels as B (column l%32 =
+// pixel, same K), so D[channel][pixel] has lane l on pixel l%32 with channels
+// 8(j/4) + 4(l/32) + j%4.  The input channels go in chunks of 32:
+//   pixels   the chunk's halo rows go from memory straight into LDS (wrap applied by the
+//            addresses, an upsampled input at its own resolution), two chunks (or tiles)
+//            ahead of the products, in three buffers with one barrier a chunk; 64 bytes a
+//            pixel, its four 16-byte groups exchanged by the column's bits 1-2 so that 8
+//            consecutive lanes' reads hit distinct banks.  With one chunk ahead, through
+//            registers, the loads' latency was not covered: without any products the
+//            network's layers took two thirds of their time.
+//   weights  straight from memory (L2) into registers, 18 operands a chunk, used for all of
+//            a wave's rows; with up to NW chunks (NW > 0) they stay there for all tiles, else
+//            (NW = 0) the next chunk's replace them as their tap row is done.
+// An input row's 6 operands are read from LDS once and serve the three output rows that use
+// it: (RW + 2) 6 reads for 18 RW products (4 rows: one read per two products), where taking
+// weights and pixels both from LDS for 64 pixels x 64 channels needed one read per product
+// and left the kernel bound by LDS (72 KB a chunk and wave, the LDS as busy as the matrix
+// cores at their peak).  The products of an output are added in the order chunk, tap,
+// channel half, whatever RW.
+// Measured in the 256x256 U-Net against 64 x 64 blocks with both operands in LDS: batch 1,
+// all layers, 248 -> 117 us; batch 32, 128x128 pixels 64 -> 64 channels 67 -> 54 us (715
+// TFLOP/s), 64x64 pixels 256 -> 128 channels 96 -> 79 us (980 TFLOP/s), 256x256 pixels 64 ->
+// 32 channels 143 -> 114 us (3.5 TB/s of unique bytes).  What is left: the matrix cores in
+// the deep layers, and memory with them in the 256x256 ones, whose workgroups' products and
+// transfers overlap in part only.
+// ---------------------------------------------------------------------------
+constexpr int RPX = 32;                // output pixels of a row tile
+
+// Epilogues (of a wave's rows, acc[r]: row r).  EPI_OUT: zout, out, pout and fout, as given;
+// EPI_HEAD: the 1x1 head; EPI_BWD + BWD_*: the backward pass's.
+enum { EPI_OUT = 0, EPI_HEAD = 1, EPI_BWD = 2 };
+
+// where a wave's rows lie: image b, rows y.. , this lane's column x; the output channels from
+// cb on
+struct RowTile {
+    int b, y, x, cb;
+};
+
+// 32 pixels x 32 channels of BF16 (row staged in so as RPX x OROW) to dst[p * cs + c], 16
+// bytes a lane: four consecutive lanes store one pixel's 64 bytes
+__device__ __forceinline__ void put_row(const ConvP& a, const RowTile& t, int r, int lane, int l32,
+                                        const __bf16* so, __bf16* dst, int cs, int c) {
+    if (t.y + r >= a.H) return;
+    const size_t p0 = ((size_t)t.b * a.H + t.y + r) * a.W + (t.x - l32);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const bf16x4 zq = *reinterpret_cast<const bf16x4*>(z + 8 * q + 4 * g);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[4 * q + e] *= silu_grad((float)zq[e]);
+    for (int k = 0; k < 2; ++k) {
+        const int px = (lane >> 2) + 16 * k, grp = lane & 3;
+        const bf16x8 v = *reinterpret_cast<const bf16x8*>(&so[px * OROW + 8 * grp]);
+        if (t.x - l32 + px < a.W)
+            *reinterpret_cast<bf16x8*>(dst + (p0 + px) * cs + c + 8 * grp) = v;
     }
 }
 
-template <int NB, int BWD>
-__device__ __forceinline__ void tile_epilogue_bwd(const ConvP& a, const f32x16 (&acc)[2][NB],
-                                                  int b, int y0, int x0, int co0, int wave,
-                                                  int l32, int g, __bf16* __restrict__ sO) {
-    const int lane = l32 + 32 * g;
-    __bf16* so = sO + wave * 64 * OROW;
+__device__ __forceinline__ void stage_row(__bf16* so, int l32, int g, const bf16x4 (&o)[4]) {
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        const int cb = co0 + nb * 32, cd = cb - a.dz_c0;   // channel of the tile, of dz
-        if (cb >= a.Cout) break;
+    for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<bf16x4*>(&so[l32 * OROW + 8 * q + 4 * g]) = o[q];
+}
+
+// Outputs.  With pout set, the stored activations of two rows also give their 2x2 averages
+// (the input of the next level's pooling layer), so that layer reads a compact quarter-size
+// tensor at its own resolution.
+template <int RW>
+__device__ __forceinline__ void rows_out(const ConvP& a, const f32x16 (&acc)[RW][1],
+                                         const RowTile& t, int lane, int l32, int g,
+                                         const float* sBias, __bf16* so) {
+    float top[16];                               // of a pooled pair of rows
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb) {
-            const int y = y0 + 4 * wave + 2 * mb + (l32 >> 4), x = x0 + (l32 & 15);
-            const bool in = y < a.H && x < a.W;
-            const size_t p = ((size_t)b * a.H + y) * a.W + x;
-            float v[16];
-            bf16x4 o[4];
-#pragma unroll
-            for (int e = 0; e < 16; ++e) v[e] = acc[mb][nb][e];
-            if constexpr (BWD == BWD_SAME) {
-                if (cd < 0) {
-                    if (in) put_f32(a, p, cb, g, v);
-                    continue;
-                }
-                if (in) silu_bwd(v, a.zin + p * a.dz_cs + cd, g);
-                to_bf16(v, 0, o);
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    *reinterpret_cast<bf16x4*>(&so[(mb * 32 + l32) * OROW + 8 * q + 4 * g]) = o[q];
-            } else if constexpr (BWD == BWD_UP) {
-                // lanes l, l^1, l^16, l^17 hold the 2x2 block
+    for (int r = 0; r < RW; ++r) {
+        float v[16];
+        bf16x4 o[4];
+        tile_values(acc, r, 0, g, sBias, v);
+        if (a.fout && t.y + r < a.H && t.x < a.W)
+            put_f32(a, ((size_t)t.b * a.H + t.y + r) * a.W + t.x, t.cb, g, v);
+        if (a.zout) {
+            to_bf16(v, 0, o);
+            stage_row(so, l32, g, o);
+            wave_lds_sync();
+            put_row(a, t, r, lane, l32, so, a.zout, a.Cout, t.cb);
+            wave_lds_sync();
+        }
+        if (a.out) {
+            to_bf16(v, a.act, o);
+            stage_row(so, l32, g, o);
+            wave_lds_sync();
+            put_row(a, t, r, lane, l32, so, a.out, a.out_cs, a.out_c0 + t.cb);
+            wave_lds_sync();
+            if (RW > 1 && a.pout) {
+                // the 2x2 averages, added in the pooling gather's order: (y, x), (y, x+1),
+                // (y+1, x), (y+1, x+1); x + 1 is lane l ^ 1's
+                float m[16];
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
-                    const float r = __shfl_xor(v[e], 1);
-                    v[e] = ((v[e] + r) + __shfl_xor(v[e], 16)) + __shfl_xor(r, 16);
+                    const float w = (float)o[e >> 2][e & 3], x1 = __shfl_xor(w, 1);
+                    m[e] = (r & 1) ? 0.25f * ((top[e] + w) + x1) : w + x1;
                 }
-                if (in && !(y & 1) && !(x & 1)) {
-                    const size_t pl = ((size_t)b * (a.H >> 1) + (y >> 1)) * (a.W >> 1) + (x >> 1);
-                    silu_bwd(v, a.zin + pl * a.dz_cs + cd, g);
-                    to_bf16(v, 0, o);
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        *reinterpret_cast<bf16x4*>(a.dz + pl * a.dz_cs + cd + 8 * q + 4 * g) = o[q];
-                }
-            } else {
-                if (!in) continue;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const size_t ph = ((size_t)b * 2 * a.H + 2 * y + (k >> 1)) * 2 * a.W + 2 * x + (k & 1);
-                    const float* sk = a.fout + ph * a.f_cs + a.f_c0 + cb + 4 * g;
-                    float t[16];
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float4 f = *reinterpret_cast<const float4*>(sk + 8 * q);
-                        t[4 * q] = fmaf(0.25f, v[4 * q], f.x);
-                        t[4 * q + 1] = fmaf(0.25f, v[4 * q + 1], f.y);
-                        t[4 * q + 2] = fmaf(0.25f, v[4 * q + 2], f.z);
-                        t[4 * q + 3] = fmaf(0.25f, v[4 * q + 3], f.w);
+                if (r & 1) {
+                    to_bf16(m, 0, o);
+                    if (!(l32 & 1)) stage_row(so, l32 >> 1, g, o);
+                    wave_lds_sync();
+                    const int pc = lane >> 2, grp = lane & 3, x = t.x - l32 + 2 * pc;
+                    const bf16x8 u = *reinterpret_cast<const bf16x8*>(&so[pc * OROW + 8 * grp]);
+                    if (x + 1 < a.W && t.y + r < a.H) {
+                        const size_t q = ((size_t)t.b * (a.H >> 1) + ((t.y + r) >> 1)) * (a.W >> 1) + (x >> 1);
+                        *reinterpret_cast<bf16x8*>(a.pout + q * a.pout_cs + t.cb + 8 * grp) = u;
                     }
-                    silu_bwd(t, a.zin + ph * a.dz_cs + cd, g);
-                    to_bf16(t, 0, o);
+                    wave_lds_sync();
+                } else {
 #pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        *reinterpret_cast<bf16x4*>(a.dz + ph * a.dz_cs + cd + 8 * q + 4 * g) = o[q];
+                    for (int e = 0; e < 16; ++e) top[e] = m[e];
                 }
             }
-        }
-        if constexpr (BWD == BWD_SAME) {
-            if (cd < 0) continue;
-            wave_lds_sync();
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int px = (lane >> 2) + 16 * k, grp = lane & 3;
-                const int pl = px & 31;
-                const int y = y0 + 4 * wave + 2 * (px >> 5) + (pl >> 4), x = x0 + (pl & 15);
-                const bf16x8 val = *reinterpret_cast<const bf16x8*>(&so[px * OROW + 8 * grp]);
-                if (y < a.H && x < a.W)
-                    *reinterpret_cast<bf16x8*>(
-                        a.dz + (((size_t)b * a.H + y) * a.W + x) * a.dz_cs + cd + 8 * grp) = val;
-            }
-            wave_lds_sync();
         }
     }
 }
@@ -501,27 +516,27 @@ __device__ __forceinline__ void head_half(const float (&v)[16], int g, const flo
                 p[k] = fmaf(v[4 * q + e], wh[k * 32 + 8 * q + 4 * g + e], p[k]);
 }
 
-// Epilogue of the last 32-channel layer at inference: its activations (rounded to BF16,
-// as they would be stored) go straight into the 1x1 head; the layer's activation tensor
-// is never written.  sH holds the head's weights and biases.
-__device__ __forceinline__ void tile_epilogue_head(const ConvP& a, const f32x16 (&acc)[2][1],
-                                                   int b, int y0, int x0, int wave, int l32,
-                                                   int g, const float* sBias, const float* sH) {
+// The last 32-channel layer at inference: its activations (rounded to BF16, as they would be
+// stored) go straight into the 1x1 head; the layer's activation tensor is never written.  sH
+// holds the head's weights and biases.
+template <int RW>
+__device__ __forceinline__ void rows_head(const ConvP& a, const f32x16 (&acc)[RW][1],
+                                          const RowTile& t, int g, const float* sBias,
+                                          const float* sH) {
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb) {
-        const int y = y0 + 4 * wave + 2 * mb + (l32 >> 4), x = x0 + (l32 & 15);
+    for (int r = 0; r < RW; ++r) {
         float v[16];
-        bf16x4 r[4];
-        tile_values(acc, mb, 0, g, sBias, v);
-        to_bf16(v, a.act, r);
+        bf16x4 b[4];
+        tile_values(acc, r, 0, g, sBias, v);
+        to_bf16(v, a.act, b);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) v[e] = (float)r[e >> 2][e & 3];
+        for (int e = 0; e < 16; ++e) v[e] = (float)b[e >> 2][e & 3];
         float p[4], o[4];
         head_half(v, g, sH, p);
 #pragma unroll
         for (int k = 0; k < 4; ++k) o[k] = __shfl_xor(p[k], 32);
-        if (g == 0 && y < a.H && x < a.W) {
-            const size_t px = ((size_t)b * a.H + y) * a.W + x;
+        if (g == 0 && t.y + r < a.H && t.x < a.W) {
+            const size_t px = ((size_t)t.b * a.H + t.y + r) * a.W + t.x;
             reinterpret_cast<float4*>(a.head_out)[px] =
                 make_float4((p[0] + o[0]) + sH[128], (p[1] + o[1]) + sH[129],
                             (p[2] + o[2]) + sH[130], (p[3] + o[3]) + sH[131]);
@@ -529,189 +544,339 @@ __device__ __forceinline__ void tile_epilogue_head(const ConvP& a, const f32x16 
     }
 }
 
-// 32-channel tiles use 50 KB of LDS, so three workgroups fit a CU (160 KB) when the
-// registers allow it; 64-channel tiles (69 KB) fit two, and so does the fused-head variant, whose
-// head arithmetic needs the registers of two workgroups per CU.
-// Epilogue variants: staged (always for 64-channel tiles; for 32-channel tiles only when
-// the layer also writes pooled output), direct, the fused 1x1 head, or one of the backward
-// pass's.
-enum { EPI_DIRECT = 0, EPI_STAGED = 1, EPI_HEAD = 2, EPI_BWD = 3 };   // EPI_BWD + BWD_*
-template <int NT, int MODE, int EPI>
-__global__ void __launch_bounds__(256, (NT == 32 && EPI < EPI_HEAD) ? 3 : 2)
-k_conv_tiled(ConvP a, int tiles_per_wg) {
-    constexpr int NB = NT / 32;
-    __shared__ __align__(16) __bf16 sA[HP * ROWA];
-    __shared__ __align__(16) __bf16 sB[NT * BPAD];
-    static_assert(4 * 64 * OROW <= HP * ROWA, "epilogue staging must fit the patch buffer");
-    static_assert((ROWA * 2 / 16) % 32 == 16, "patch rows 16 mod 32 16-byte units apart");
-    static_assert(EPI != EPI_HEAD || (NT == 32 && MODE == MODE_SAME), "head fusion: 32 channels");
-    __shared__ float sH[EPI == EPI_HEAD ? 4 * 32 + 4 : 1];
-    __shared__ __align__(16) float sBias[NT];
-    if (threadIdx.x < NT)   // ordered before use by the first tile's barriers, as sH
-        sBias[threadIdx.x] = a.bias && (int)(blockIdx.y * NT + threadIdx.x) < a.Cout
-                                 ? a.bias[blockIdx.y * NT + threadIdx.x] : 0.0f;
-    if constexpr (EPI == EPI_HEAD) {   // ordered before use by the first tile's barriers
+// The backward pass: a layer's input gradient goes straight into the dz of the layer that
+// produced the input, dz = (gradient of its activation) silu'(z), rounded to BF16 once, so
+// that the FP32 gradients (4 and more bytes a value, written and read again) stay in
+// registers.  Each gradient is formed as by separate passes, in the same order.
+//   BWD_SAME  the producer is at the same resolution.  Channels below a.dz_c0 belong to a
+//             skip connection, whose gradient gets a second part later: stored to a.fout.
+//   BWD_UP    the input was upsampled: the 2x2 sum of the gradient, at half resolution.
+//   BWD_POOL  the input was pooled: a quarter of the gradient on each of four pixels at
+//             double resolution, added to the skip connection's in a.fout.
+// (Gradients of 16 samples of 256x256: 725 us of element-wise kernels before, none now.)
+__device__ __forceinline__ void silu_bwd(float (&v)[16], const __bf16* z, int g) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const bf16x4 zq = *reinterpret_cast<const bf16x4*>(z + 8 * q + 4 * g);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[4 * q + e] *= silu_grad((float)zq[e]);
+    }
+}
+
+template <int RW, int BWD>
+__device__ __forceinline__ void rows_bwd(const ConvP& a, const f32x16 (&acc)[RW][1],
+                                         const RowTile& t, int lane, int l32, int g, __bf16* so) {
+    const int cd = t.cb - a.dz_c0;               // channel of dz
+    if constexpr (BWD == BWD_SAME) {
+        if (cd < 0) {
+#pragma unroll
+            for (int r = 0; r < RW; ++r)
+                if (t.y + r < a.H && t.x < a.W) {
+                    float v[16];
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) v[e] = acc[r][0][e];
+                    put_f32(a, ((size_t)t.b * a.H + t.y + r) * a.W + t.x, t.cb, g, v);
+                }
+            return;
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+        const bool in = t.y + r < a.H && t.x < a.W;
+        float v[16];
+        bf16x4 o[4];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) v[e] = acc[r][0][e];
+        if constexpr (BWD == BWD_SAME) {
+            if (in) silu_bwd(v, a.zin + (((size_t)t.b * a.H + t.y + r) * a.W + t.x) * a.dz_cs + cd, g);
+            to_bf16(v, 0, o);
+            stage_row(so, l32, g, o);
+            wave_lds_sync();
+            put_row(a, t, r, lane, l32, so, a.dz, a.dz_cs, cd);
+            wave_lds_sync();
+        } else if constexpr (BWD == BWD_UP) {
+            if (r & 1) continue;                 // a block's rows are r and r + 1, its lanes l, l^1
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const float w = acc[r + (RW > 1)][0][e];
+                v[e] = ((v[e] + __shfl_xor(v[e], 1)) + w) + __shfl_xor(w, 1);
+            }
+            if (in && !(t.x & 1)) {
+                const size_t pl = ((size_t)t.b * (a.H >> 1) + ((t.y + r) >> 1)) * (a.W >> 1) + (t.x >> 1);
+                silu_bwd(v, a.zin + pl * a.dz_cs + cd, g);
+                to_bf16(v, 0, o);
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<bf16x4*>(a.dz + pl * a.dz_cs + cd + 8 * q + 4 * g) = o[q];
+            }
+        } else {
+            if (!in) continue;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const size_t ph = ((size_t)t.b * 2 * a.H + 2 * (t.y + r) + (k >> 1)) * 2 * a.W +
+                                  2 * t.x + (k & 1);
+                const float* sk = a.fout + ph * a.f_cs + a.f_c0 + t.cb + 4 * g;
+                float u[16];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float4 f = *reinterpret_cast<const float4*>(sk + 8 * q);
+                    u[4 * q] = fmaf(0.25f, v[4 * q], f.x);
+                    u[4 * q + 1] = fmaf(0.25f, v[4 * q + 1], f.y);
+                    u[4 * q + 2] = fmaf(0.25f, v[4 * q + 2], f.z);
+                    u[4 * q + 3] = fmaf(0.25f, v[4 * q + 3], f.w);
+                }
+                silu_bwd(u, a.zin + ph * a.dz_cs + cd, g);
+                to_bf16(u, 0, o);
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<bf16x4*>(a.dz + ph * a.dz_cs + cd + 8 * q + 4 * g) = o[q];
+            }
+        }
+    }
+}
+
+template <int NCB, int RW, int NW, int MODE, int EPI, bool BIG>
+__global__ void __launch_bounds__(256, 2) k_conv_rows(ConvP a, int tiles_per_wg) {
+    constexpr int RG = 4 / NCB, ROWS = RG * RW;               // row groups, rows of a tile
+    constexpr int XR = MODE == MODE_UP ? ROWS / 2 + 2 : ROWS + 2;
+    constexpr int XC = MODE == MODE_UP ? RPX / 2 + 2 : RPX + 2;
+    constexpr int ITEMS = XR * XC * 4, NI = (ITEMS + 255) / 256;   // 16-byte items
+    constexpr int BUF = (ITEMS + 63) / 64 * 64 * 8;           // whole waves of items, in BF16
+    static_assert(MODE != MODE_UP || ROWS % 2 == 0, "whole rows of the upsampled input");
+    static_assert(EPI != EPI_BWD + BWD_UP || RW % 2 == 0, "a 2x2 block's rows are in one wave");
+    static_assert(XC * 64 % 128 == 0, "a row's first pixel starts a line of banks");
+    // One object: with several, the compiler marks which one an access is to, and has every
+    // read of the pixels wait for all loads to LDS in flight, the latest included
+    struct Shared {
+        __bf16 a[3 * BUF], o[4][RPX * OROW];
+        float bias[32 * NCB], head[EPI == EPI_HEAD ? 4 * 32 + 4 : 1];
+    };
+    __shared__ __align__(16) Shared sh;
+    __bf16* const sA = sh.a;
+    float *const sBias = sh.bias, *const sH = sh.head;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    __bf16* const sO = sh.o[wave];
+    const int l32 = lane & 31, g = lane >> 5;
+    const int wcb = wave % NCB, rg = wave / NCB;              // the wave's channel block, rows
+    const int cb0 = blockIdx.y * 32 * NCB, cb = cb0 + 32 * wcb;
+    if (threadIdx.x < 32 * NCB) sBias[threadIdx.x] = a.bias ? a.bias[cb0 + threadIdx.x] : 0.0f;
+    if constexpr (EPI == EPI_HEAD)
         for (int i = threadIdx.x; i < 4 * 32 + 4; i += 256)
             sH[i] = i < 128 ? a.head_w[i] : a.head_b[i - 128];
-    }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int l32 = lane & 31, g = lane >> 5;
-    const int tx_n = (a.W + TP - 1) / TP, ty_n = (a.H + TP - 1) / TP;
+    const int tx_n = (a.W + RPX - 1) / RPX, ty_n = (a.H + ROWS - 1) / ROWS;
     const int ntile = a.B * tx_n * ty_n;
-    const int t_beg = blockIdx.x * tiles_per_wg;
+    // a contiguous run of tiles per XCD (workgroups go round the 8 of them), so that the halos
+    // that neighbouring tiles share are read from memory once and then from that XCD's L2
+    const int xcd = blockIdx.x % 8, xq = gridDim.x / 8, xr = gridDim.x % 8;
+    const int t_beg = (xcd * xq + min(xcd, xr) + (int)blockIdx.x / 8) * tiles_per_wg;
     const int t_end = min(ntile, t_beg + tiles_per_wg);
-    const int co0 = blockIdx.y * NT;
-    const int C = a.g.C;
-    const int nchunk = C / 32;
-    // the (tile, chunk) pairs of this workgroup, in order; with one chunk the weights
-    // are staged once
-    const int niter = (t_end - t_beg) * nchunk;
-
-    auto tile_xy = [&](int t, int& b, int& y0, int& x0) {
-        const int tx = t % tx_n;
-        t /= tx_n;
+    if (t_beg >= t_end) return;
+    const int nchunk = NW > 0 ? NW : a.g.C / 32;
+    auto tile_at = [&](int t, int& b, int& y0, int& x0) {      // down the columns
         const int ty = t % ty_n;
-        b = t / ty_n;
-        x0 = tx * TP;
-        y0 = ty * TP;
+        t /= ty_n;
+        const int tx = t % tx_n;
+        b = t / tx_n;
+        x0 = tx * RPX;
+        y0 = ty * ROWS;
     };
 
-    // The weights go a tap (64 channels) or two (32) at a time, 4 groups of 8 input channels
-    // an output channel.
-    constexpr int XE = MODE == MODE_UP ? UPH : HP;   // an upsampled input is staged as it lies
-    constexpr int TSTEP = 64 / NT;                   // taps a load of the workgroup covers
-    constexpr int B_PER_T = (9 + TSTEP - 1) / TSTEP;
-    const HaloCols<XE> hc;
-    const int bcol = (threadIdx.x >> 2) % NT, btap = (threadIdx.x >> 2) / NT;
-    bf16x8 ra[hc.N], rb[B_PER_T];
-    auto load_a = [&](int it) {
-        int b, y0, x0;
-        tile_xy(t_beg + it / nchunk, b, y0, x0);
-        const int c0 = (it % nchunk) * 32;
-        if constexpr (MODE == MODE_UP) {
-            hc.load(a.g, b, y0 / 2 - 1, x0 / 2 - 1, c0, ra);
-        } else if constexpr (MODE == MODE_SAME) {
-            hc.load(a.g, b, y0 - 1, x0 - 1, c0, ra);
-        } else {
-#pragma unroll
-            for (int k = 0; k < hc.N; ++k)
-                if (hc.has(k))
-                    ra[k] = gather8<MODE>(a.g, b, halo(y0 - 1 + hc.row0 + k, a.H),
-                                          halo(x0 - 1 + (hc.col >> 2), a.W), c0 + 8 * (hc.col & 3));
-        }
+    // pixels: the tile and chunk to fetch next, and this thread's items of that tile's halo as
+    // offsets (in 16 bytes) into its image
+    int ft = t_beg, fch = 0, fb = 0, fy = 0, fx = 0;
+    uint32_t off[NI];
+    const uint32_t img_items = (uint32_t)a.g.Hin * (uint32_t)a.g.Win * (uint32_t)(a.g.cs >> 3);
+    auto image = [&]() { return a.g.p + (size_t)fb * img_items * 8 + a.g.c0; };
+    auto window = [&]() {                                     // the image in elements of 16 bytes
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(image()), 16, img_items, 0x00027000);
     };
-    auto store_a = [&]() {
+    auto img = window();
+    const __bf16* big = nullptr;
+    auto aim = [&]() {
+        tile_at(ft, fb, fy, fx);
+        if constexpr (BIG) big = image();
+        else img = window();
+        const int yb = (MODE == MODE_UP ? fy / 2 : fy) - 1, xb = (MODE == MODE_UP ? fx / 2 : fx) - 1;
+        if constexpr (MODE != MODE_POOL)
 #pragma unroll
-        for (int k = 0; k < hc.N; ++k)
-            if (hc.has(k))
-                *reinterpret_cast<bf16x8*>(&sA[(hc.row0 + k) * ROWA + (hc.col >> 2) * APAD +
-                                               8 * (hc.col & 3)]) = ra[k];
-    };
-    auto load_b = [&](int it) {
-        const __bf16* w = a.w + ((size_t)(co0 + bcol) * 9 + btap) * C + (it % nchunk) * 32 +
-                          8 * (threadIdx.x & 3);
-#pragma unroll
-        for (int k = 0; k < B_PER_T; ++k)
-            if (TSTEP * k + btap < 9) rb[k] = *reinterpret_cast<const bf16x8*>(w + (size_t)k * TSTEP * C);
-    };
-    auto store_b = [&]() {
-#pragma unroll
-        for (int k = 0; k < B_PER_T; ++k)
-            if (TSTEP * k + btap < 9)
-                *reinterpret_cast<bf16x8*>(&sB[bcol * BPAD + (TSTEP * k + btap) * 32 +
-                                               8 * (threadIdx.x & 3)]) = rb[k];
-    };
-
-    f32x16 acc[2][NB];
-    // this lane's pixel in each row block: patch row 4w + 2mb + l32/16, column l32%16
-    const int prow = 4 * wave + (l32 >> 4), pcol = l32 & 15;
-    // where it reads its operands: halo position (prow + 2 mb + dy, pcol + dx), for an
-    // upsampled input that position halved, (v + 1) >> 1 (prow - l32/16 is even: tap row 0
-    // reads the lane's own row, 1 the middle one of all, 2 the one after the lane's own)
-    const __bf16* pa[2][2];
-#pragma unroll
-    for (int odd = 0; odd < 2; ++odd) {
-        pa[0][odd] = &sA[(2 * wave + (l32 >> 4)) * ROWA + ((pcol + odd + 1) >> 1) * APAD + 8 * g];
-        pa[1][odd] = &sA[(2 * wave + 1) * ROWA + ((pcol + odd + 1) >> 1) * APAD + 8 * g];
-    }
-
-    if (niter > 0) {
-        load_b(0);
-        if (MODE != MODE_POOL) load_a(0);
-    }
-    for (int it = 0; it < niter; ++it) {
-        const int ch = it % nchunk;
-        if (ch == 0) {
-#pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) acc[mb][nb][j] = 0.0f;
-        }
-        __syncthreads();                         // the previous chunk is consumed
-        if (MODE == MODE_POOL) load_a(it);       // pooled gathers average at once
-        store_a();
-        if (nchunk > 1 || it == 0) store_b();
-        __syncthreads();
-        if (it + 1 < niter) {
-            if (nchunk > 1) load_b(it + 1);
-            if (MODE != MODE_POOL) load_a(it + 1);
-        }
-        // K steps s = 2 tap + h (h: the half of the chunk's 32 channels), the operands of
-        // step s + 1 read from LDS ahead of step s's MFMAs, so that the MFMAs cover the
-        // reads' latency (the accumulation order is unchanged)
-        auto ld = [&](int s, bf16x8 (&A)[2], bf16x8 (&Bm)[NB]) {
-            const int tap = s >> 1, h = s & 1;
-            const int dy = tap / 3, dx = tap % 3;   // halo coordinates: +1 offset folded in
-#pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
-                A[mb] = *reinterpret_cast<const bf16x8*>(
-                    MODE == MODE_UP
-                        ? pa[dy & 1][dx & 1] + (mb + (dy >> 1)) * ROWA + (dx >> 1) * APAD + 16 * h
-                        : &sA[(prow + 2 * mb + dy) * ROWA + (pcol + dx) * APAD + 16 * h + 8 * g]);
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-                Bm[nb] = *reinterpret_cast<const bf16x8*>(
-                    &sB[(nb * 32 + l32) * BPAD + tap * 32 + 16 * h + 8 * g]);
-        };
-        bf16x8 Ac[2], Bc[NB];
-        ld(0, Ac, Bc);
-#pragma unroll
-        for (int s = 0; s < 18; ++s) {
-            bf16x8 An[2], Bn[NB];
-            if (s + 1 < 18) ld(s + 1, An, Bn);
-#pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
-                    acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(Bc[nb], Ac[mb],
-                                                                         acc[mb][nb], 0, 0, 0);
-            if (s + 1 < 18) {
-                __builtin_amdgcn_sched_group_barrier(0x100, 2 + NB, 0);   // the next reads,
-                __builtin_amdgcn_sched_group_barrier(0x008, 2 * NB, 0);   // then these MFMAs
-#pragma unroll
-                for (int mb = 0; mb < 2; ++mb) Ac[mb] = An[mb];
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb) Bc[nb] = Bn[nb];
+            for (int k = 0; k < NI; ++k) {
+                const int first = (k + 1) * 256 > ITEMS && k * 256 + wave * 64 >= ITEMS
+                                      ? wave * 64 : k * 256 + wave * 64;
+                const int it = min(first + lane, ITEMS - 1);
+                const int pix = it >> 2, r = pix / XC, c = pix - r * XC;
+                off[k] = ((uint32_t)halo(yb + r, a.g.Hin) * (uint32_t)a.g.Win +
+                          (uint32_t)halo(xb + c, a.g.Win)) * (uint32_t)(a.g.cs >> 3) +
+                         ((it & 3) ^ ((c >> 1) & 3));
             }
-        }
-        if (ch == nchunk - 1) {
-            int b, y0, x0;
-            tile_xy(t_beg + it / nchunk, b, y0, x0);
-            if constexpr (EPI == EPI_STAGED) {
-                __syncthreads();                 // every wave is done reading the patch
-                tile_epilogue_staged<NB>(a, acc, b, y0, x0, co0, wave, l32, g, sBias, sA);
-            } else if constexpr (EPI >= EPI_BWD) {
-                if (EPI == EPI_BWD + BWD_SAME) __syncthreads();
-                tile_epilogue_bwd<NB, EPI - EPI_BWD>(a, acc, b, y0, x0, co0, wave, l32, g, sA);
-            } else if constexpr (EPI == EPI_HEAD) {
-                tile_epilogue_head(a, acc, b, y0, x0, wave, l32, g, sBias, sH);
+    };
+    // fetch it into buffer `to`.  Every wave issues NI loads on every path, past the last
+    // item its first one again and past the last tile that tile again (into a buffer that is
+    // not read any more), so that the compiler and arrive() know how many are outstanding:
+    // behind a branch, the streamed weights' waits would take in these loads too
+    auto fetch = [&](int to) {
+#pragma unroll
+        for (int k = 0; k < NI; ++k) {
+            const int first = (k + 1) * 256 > ITEMS && k * 256 + wave * 64 >= ITEMS
+                                  ? wave * 64 : k * 256 + wave * 64;
+            __bf16* dst = &sA[to * BUF + first * 8];
+            if constexpr (MODE == MODE_POOL) {
+                const int it = min(first + lane, ITEMS - 1);
+                const int pix = it >> 2, r = pix / XC, c = pix - r * XC;
+                *reinterpret_cast<bf16x8*>(dst + lane * 8) = gather8<MODE_POOL>(
+                    a.g, fb, halo(fy - 1 + r, a.H), halo(fx - 1 + c, a.W),
+                    32 * fch + 8 * ((it & 3) ^ ((c >> 1) & 3)));
             } else {
-                tile_epilogue_direct<NB>(a, acc, b, y0, x0, co0, wave, l32, g, sBias);
+                typedef __attribute__((address_space(3))) void* to_t;
+                typedef const __attribute__((address_space(1))) void* from_t;
+                if constexpr (BIG) {
+                    // the compiler takes these for flat accesses and waits for all of them
+                    // where it would wait for some of the streamed weights
+                    __builtin_amdgcn_global_load_lds((from_t)(big + 32 * fch + (size_t)off[k] * 8),
+                                                     (to_t)dst, 16, 0, 0);
+                } else {
+#ifdef __HIP_DEVICE_COMPILE__                                  // (unknown to the host's pass)
+                    __builtin_amdgcn_struct_ptr_buffer_load_lds(img, (to_t)dst, 16, off[k], 0,
+                                                                64 * fch, 0, 0);
+#endif
+                }
             }
         }
+        if (++fch == nchunk) {
+            fch = 0;
+            if (ft + 1 < t_end) {
+                ++ft;
+                aim();
+            }
+        }
+    };
+
+    // weights: operand (tap, h) is channels 16h..+15 of the chunk; packed (weights_bf16) they
+    // are 1 KB runs in the order lanes take them.  Through a buffer descriptor, so that an
+    // address is a lane's offset plus a scalar
+    bf16x8 W[NW > 0 ? NW : 1][9][2];
+    const auto wsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<__bf16*>(a.w), 0, a.Cout * 9 * a.g.C * 2, 0x00027000);
+    const int wchunk = a.packed ? a.Cout / 32 * 18 * 1024 : 64;
+    const int wtap = a.packed ? 2048 : a.g.C * 2, whalf = a.packed ? 1024 : 32;
+    const int wlane = a.packed ? cb / 32 * 18 * 1024 + lane * 16 : (cb + l32) * 9 * a.g.C * 2 + 16 * g;
+    auto load_w = [&](int into, int chunk, int dy) {
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                W[into][3 * dy + dx][h] = __builtin_bit_cast(
+                    bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
+                                wsrc, wlane, chunk * wchunk + (3 * dy + dx) * wtap + h * whalf, 0));
+    };
+
+    // where the lane reads its operands: position (rg RW + i, l32 + dx) of the halo, halved
+    // ((v + 1) >> 1) for an upsampled input (rg RW is even there, or RW is 1); pat[.][dx][h]
+    // for the first rows of each kind
+    constexpr int RK = MODE == MODE_UP ? 2 : 1;
+    int pat[RK][3][2];
+#pragma unroll
+    for (int i = 0; i < RK; ++i)
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int row = MODE == MODE_UP ? (rg * RW + i + 1) >> 1 : rg * RW;
+                const int col = MODE == MODE_UP ? (l32 + dx + 1) >> 1 : l32 + dx;
+                pat[i][dx][h] = (row * XC + col) * 32 + 8 * ((2 * h + g) ^ ((col >> 1) & 3));
+            }
+
+    f32x16 acc[RW][1];
+    // The products of one chunk, from buffer `from` with weights W[w]; `next`: the chunk whose
+    // weights replace them (streamed weights only).  Input row i of the wave's halo gives 6
+    // operands (dx, h), each for the output rows i - dy; operand s = 6 i + 2 dx + h is read
+    // two ahead of its products.
+    auto products = [&](int from, auto w_, int next) {
+        constexpr int w = decltype(w_)::value;
+        const __bf16* px = &sA[from * BUF];
+        auto pixels = [&](int s) {
+            const int i = s / 6;
+            const __bf16* q = px + pat[i % RK][s % 6 / 2][s & 1] + i / RK * XC * 32;
+            return *reinterpret_cast<const bf16x8*>(q);
+        };
+        constexpr int NS = 6 * (RW + 2);
+        bf16x8 F[3];
+        F[0] = pixels(0);
+        F[1] = pixels(1);
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const int i = s / 6, k = s % 6;
+            if (s + 2 < NS) F[(s + 2) % 3] = pixels(s + 2);
+#pragma unroll
+            for (int dy = 2; dy >= 0; --dy) {
+                const int r = i - dy;
+                if (r < 0 || r >= RW) continue;
+                acc[r][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(W[w][3 * dy + k / 2][k & 1],
+                                                                    F[s % 3], acc[r][0], 0, 0, 0);
+            }
+            // the order to keep: the read two ahead, then these products
+            if (s + 2 < NS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            const int n = (i < 2 ? i : 2) - (i < RW ? 0 : i - RW + 1) + 1;
+            if (n == 1) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            if (n == 2) __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+            if (n == 3) __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
+            // tap row dy is done after input row RW - 1 + dy
+            if (NW == 0 && k == 5 && i >= RW - 1) load_w(0, next, i - (RW - 1));
+        }
+    };
+    // End of a chunk's products: this wave's part of the next chunk has to be in LDS, then
+    // every wave's.  Loads complete in order, and that fetch was followed by the latest one's
+    // NI and by the streamed weights of two chunks: so many may be outstanding.
+    auto arrive = [&]() {
+        constexpr int LATER = (NW == 0 ? 36 : 0) + NI;
+        static_assert(LATER < 64, "the counter has six bits");
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LATER) : "memory");
+    };
+
+    aim();
+    fetch(0);
+    fetch(1);
+    if constexpr (NW > 0)
+        static_for<0, NW>([&](auto c_) {
+            constexpr int c = decltype(c_)::value;
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy) load_w(c, c, dy);
+        });
+    else
+#pragma unroll
+        for (int dy = 0; dy < 3; ++dy) load_w(0, 0, dy);
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    int buf = 0;
+    for (int t = t_beg; t < t_end; ++t) {
+        RowTile at;
+        int y0, x0;
+        tile_at(t, at.b, y0, x0);
+        at.y = y0 + rg * RW;
+        at.x = x0 + l32;
+        at.cb = cb;
+#pragma unroll
+        for (int r = 0; r < RW; ++r)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) acc[r][0][j] = 0.0f;
+        auto chunk = [&](auto w_, int next) {
+            const int two = buf == 0 ? 2 : buf - 1;          // (buf + 2) % 3
+            fetch(two);
+            __builtin_amdgcn_sched_barrier(0);               // arrive() counts what follows it
+            products(buf, w_, next);
+            arrive();
+            buf = buf == 2 ? 0 : buf + 1;
+        };
+        if constexpr (NW > 0) {
+            static_for<0, NW>([&](auto c_) { chunk(c_, 0); });
+        } else {
+            for (int ch = 0; ch < nchunk; ++ch)
+                chunk(std::integral_constant<int, 0>{}, ch + 1 == nchunk ? 0 : ch + 1);
+        }
+        if constexpr (EPI == EPI_OUT) rows_out<RW>(a, acc, at, lane, l32, g, sBias + 32 * wcb, sO);
+        else if constexpr (EPI == EPI_HEAD) rows_head<RW>(a, acc, at, g, sBias + 32 * wcb, sH);
+        else rows_bwd<RW, EPI - EPI_BWD>(a, acc, at, lane, l32, g, sO);
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // no load outlives its LDS
 }
 
 // ---------------------------------------------------------------------------
@@ -781,8 +946,8 @@ __global__ void __launch_bounds__(256, 2) k_conv_first(ConvP a) {
 // the first layer's activations on its 18x18 halo patch; it computes them from a 20x20
 // patch of the input with k_conv_first's MFMA sequence, bias, SiLU and BF16 rounding (so
 // they are bitwise the values the first layer would have stored, the periodic wrap
-// commuting with the convolution) and writes them where k_conv_tiled stages its input;
-// the second layer then runs as k_conv_tiled<32> with the staged epilogue.  Both layers'
+// commuting with the convolution) and writes them to LDS as the second layer's input patch;
+// the second layer's products (k_conv_rows' order) and its epilogue follow.  Both layers'
 // weight operands stay in registers; workgroups walk runs of tiles with the next tile's
 // input loads in flight.  The first layer's activations never reach HBM; training keeps
 // the two layers apart (its backward pass needs them).  Needs H, W >= 16 (one period of
@@ -834,8 +999,7 @@ __global__ void __launch_bounds__(256, 2) k_conv_stem(ConvP a0, ConvP a, int til
             }
         }
     };
-    // both layers' weight operands, held in registers for the workgroup's life (the
-    // values k_conv_first and k_conv_tiled stage in LDS): lane l32 is output channel l32;
+    // both layers' weight operands, held in registers for the workgroup's life: lane l32 is output channel l32;
     // first layer: taps 2s + g (the tenth zero) of 8 channels; second layer: tap t, input
     // channels 16h + 8g .. + 7
     bf16x8 w0[5], w1[9][2];
@@ -849,8 +1013,7 @@ __global__ void __launch_bounds__(256, 2) k_conv_stem(ConvP a0, ConvP a, int til
     for (int tap = 0; tap < 9; ++tap)
 #pragma unroll
         for (int h = 0; h < 2; ++h)
-            w1[tap][h] = *reinterpret_cast<const bf16x8*>(a.w + ((size_t)l32 * 9 + tap) * 32 +
-                                                          16 * h + 8 * g);
+            w1[tap][h] = *reinterpret_cast<const bf16x8*>(a.w + ((2 * tap + h) * 64 + lane) * 8);
     if (t_beg < t_end) load_x(t_beg);
     for (int t = t_beg; t < t_end; ++t) {
         int b, y0, x0;
@@ -894,7 +1057,7 @@ __global__ void __launch_bounds__(256, 2) k_conv_stem(ConvP a0, ConvP a, int til
             }
         }
         __syncthreads();
-        // the second layer, as k_conv_tiled<32> over its one input chunk
+        // the second layer, over its one input chunk
         f32x16 acc[2][1];
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb)
@@ -902,7 +1065,7 @@ __global__ void __launch_bounds__(256, 2) k_conv_stem(ConvP a0, ConvP a, int til
             for (int j = 0; j < 16; ++j) acc[mb][0][j] = 0.0f;
         const int prow = 4 * wave + (l32 >> 4), pcol = l32 & 15;
         // K steps s = 2 tap + h, the patch operands of step s + 1 read ahead of step s's
-        // MFMAs (as in k_conv_tiled; the accumulation order is unchanged)
+        // MFMAs
         auto ld = [&](int s, bf16x8 (&A)[2]) {
             const int tap = s >> 1, h = s & 1;
             const int dy = tap / 3, dx = tap % 3;
@@ -1276,8 +1439,17 @@ __global__ void k_adam(float* __restrict__ w, const float* __restrict__ g, float
     w[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + 1e-8f);
 }
 
-// BF16 copies of one layer's weights: wf [Cout][9][Cin] and, for the input gradient,
-// wt [Cin][9][Cout] with the taps mirrored (tap -> 8 - tap)
+// Position of the weight of output channel o, tap, input channel c (Cout x 9 x C of them) in
+// the order the row kernel's lanes take them: [chunk of 32 c][block of 32 o][tap][16 c][8 c]
+// [o][8]
+__device__ __forceinline__ size_t packed_at(int Cout, int o, int tap, int c) {
+    const size_t block = (size_t)(c >> 5) * (Cout >> 5) + (o >> 5);
+    return ((block * 18 + 2 * tap + ((c >> 4) & 1)) * 64 + ((c >> 3) & 1) * 32 + (o & 31)) * 8 + (c & 7);
+}
+
+// BF16 copies of one layer's weights w [Cout][9][Cin]: wf in packed order (the first layer's
+// 8 input channels as they are) and, for the input gradient, wt, the weights of a layer Cout
+// -> Cin with the taps mirrored (tap -> 8 - tap), packed
 __global__ void k_weights_bf16(const float* __restrict__ w, int Cout, int Cin, __bf16* __restrict__ wf,
                                __bf16* __restrict__ wt) {
     const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
@@ -1286,8 +1458,9 @@ __global__ void k_weights_bf16(const float* __restrict__ w, int Cout, int Cin, _
     const int ci = (int)(i % Cin);
     const int tap = (int)((i / Cin) % 9);
     const int co = (int)(i / (9 * (size_t)Cin));
-    wf[i] = (__bf16)w[i];
-    if (wt) wt[((size_t)ci * 9 + (8 - tap)) * Cout + co] = (__bf16)w[i];
+    const bool packed = Cin % 32 == 0;
+    wf[packed ? packed_at(Cout, co, tap, ci) : i] = (__bf16)w[i];
+    if (wt && packed) wt[packed_at(Cin, ci, 8 - tap, co)] = (__bf16)w[i];
 }
 
 // density of sample b at order parameter phi (clamped: phi overshoots [0, 1] slightly and
@@ -1439,58 +1612,71 @@ __global__ void __launch_bounds__(256) k_sum_field(const float* __restrict__ a, 
 // ---------------------------------------------------------------------------
 static inline unsigned blocks(size_t n) { return (unsigned)((n + 255) / 256); }
 
-template <int NT>
-static hipError_t launch_tiled(const ConvP& a, hipStream_t st) {
-    // as many workgroups as are resident at once (3 per CU for 32-channel tiles, 2 for
-    // 64-channel tiles and the fused-head variant, as their launch bounds say); each walks
-    // a contiguous run of tiles so that the loads of its next tile overlap the MFMAs of
-    // the current one
-    const int resident = NT == 32 && !a.head_out && a.bwd < 0 ? 768 : 512;
-    const int ntile = a.B * ((a.H + TP - 1) / TP) * ((a.W + TP - 1) / TP);
-    const int nblk_n = (a.Cout + NT - 1) / NT;
-    const int per = std::max(1, (ntile * nblk_n + resident - 1) / resident);
-    const dim3 grid((ntile + per - 1) / per, nblk_n);
-    if (a.pout && (a.H % 2 || a.W % 2 || !a.out || (NT == 32 && a.g.mode != MODE_SAME)))
-        return hipErrorInvalidValue;
-    constexpr int E = NT == 64 ? EPI_STAGED : EPI_DIRECT;
+template <int NCB, int RW, int NW, int MODE, int EPI, bool BIG = false>
+static hipError_t launch_rows_k(const ConvP& a, hipStream_t st) {
+    // as many workgroups as are resident at once (2 per CU); each walks a contiguous run of
+    // tiles so that the loads of its next tiles overlap the products of the current one
+    constexpr int ROWS = 4 / NCB * RW;
+    const int ntile = a.B * ((a.H + ROWS - 1) / ROWS) * ((a.W + RPX - 1) / RPX);
+    const int nblk_n = a.Cout / (32 * NCB);
+    const int per = std::max(1, (ntile * nblk_n + 511) / 512);
+    hipLaunchKernelGGL((k_conv_rows<NCB, RW, NW, MODE, EPI, BIG>), dim3((ntile + per - 1) / per, nblk_n),
+                       dim3(256), 0, st, a, per);
+    return hipGetLastError();
+}
+
+template <int NCB, int RW, int MODE, int EPI>
+static hipError_t launch_rows_c(const ConvP& a, hipStream_t st) {
+    // weights resident for one chunk, or two where the registers allow it
+    if (a.g.C == 32) return launch_rows_k<NCB, RW, 1, MODE, EPI>(a, st);
+    if constexpr (RW <= 2 && (RW == 1 || (EPI != EPI_HEAD && EPI != EPI_BWD + BWD_SAME)))
+        if (a.g.C == 64) return launch_rows_k<NCB, RW, 2, MODE, EPI>(a, st);
+    return launch_rows_k<NCB, RW, 0, MODE, EPI>(a, st);
+}
+
+template <int NCB, int MODE, int EPI>
+static hipError_t launch_rows_w(const ConvP& a, hipStream_t st) {
+    // rows per wave: 4 (one channel block a workgroup: 2, as LDS holds two workgroups of 8
+    // rows a CU; 64 input channels: 2, with both chunks' weights resident) where that gives
+    // every CU two workgroups, fewer for small batches, whose latency counts (a pooled output
+    // and an upsampled input's gradient need pairs of rows in one wave)
+    const auto wgs = [&](int rw) {
+        const int rows = 4 / NCB * rw;
+        return (long)a.B * ((a.H + rows - 1) / rows) * ((a.W + RPX - 1) / RPX) * (a.Cout / (32 * NCB));
+    };
+    // (a buffer's address arithmetic has 32 bits: images of 4 GiB and more take plain addresses)
+    if constexpr (MODE != MODE_POOL)
+        if ((double)a.g.Hin * a.g.Win * a.g.cs * 2 >= 4294967296.0)
+            return launch_rows_k<NCB, 2, 0, MODE, EPI, true>(a, st);
+    if constexpr (NCB == 2)
+        if (wgs(4) >= 512 && a.g.C != 64) return launch_rows_c<NCB, 4, MODE, EPI>(a, st);
+    if constexpr (EPI != EPI_BWD + BWD_UP)
+        if (wgs(2) < 512 && !a.pout) return launch_rows_c<NCB, 1, MODE, EPI>(a, st);
+    return launch_rows_c<NCB, 2, MODE, EPI>(a, st);
+}
+
+template <int NCB>
+static hipError_t launch_rows(const ConvP& a, hipStream_t st) {
+    if (a.pout && (a.H % 2 || a.W % 2 || !a.out)) return hipErrorInvalidValue;
     if (a.bwd >= 0) {
         if (a.g.mode != MODE_SAME || !a.zin || !a.dz || a.bias || a.zout || a.out || a.pout ||
             a.head_out || a.dz_c0 % 32 || (a.bwd != BWD_SAME && a.dz_c0) ||
             (a.bwd == BWD_POOL && !a.fout) || (a.dz_c0 && !a.fout) ||
             (a.bwd == BWD_UP && (a.H % 2 || a.W % 2)))
             return hipErrorInvalidValue;
-        if (a.bwd == BWD_SAME)
-            hipLaunchKernelGGL((k_conv_tiled<NT, MODE_SAME, EPI_BWD + BWD_SAME>), grid, dim3(256),
-                               0, st, a, per);
-        else if (a.bwd == BWD_UP)
-            hipLaunchKernelGGL((k_conv_tiled<NT, MODE_SAME, EPI_BWD + BWD_UP>), grid, dim3(256), 0,
-                               st, a, per);
-        else
-            hipLaunchKernelGGL((k_conv_tiled<NT, MODE_SAME, EPI_BWD + BWD_POOL>), grid, dim3(256),
-                               0, st, a, per);
-        return hipGetLastError();
+        if (a.bwd == BWD_SAME) return launch_rows_w<NCB, MODE_SAME, EPI_BWD + BWD_SAME>(a, st);
+        if (a.bwd == BWD_UP) return launch_rows_w<NCB, MODE_SAME, EPI_BWD + BWD_UP>(a, st);
+        return launch_rows_w<NCB, MODE_SAME, EPI_BWD + BWD_POOL>(a, st);
     }
     if (a.head_out) {
-        if constexpr (NT == 32) {
-            if (a.Cout != 32 || a.g.mode != MODE_SAME || a.out || a.zout || a.fout || a.pout ||
-                !a.head_w || !a.head_b)
-                return hipErrorInvalidValue;
-            hipLaunchKernelGGL((k_conv_tiled<32, MODE_SAME, EPI_HEAD>), grid, dim3(256), 0, st,
-                               a, per);
-            return hipGetLastError();
-        }
-        return hipErrorInvalidValue;
+        if (NCB != 1 || a.Cout != 32 || a.g.mode != MODE_SAME || a.out || a.zout || a.fout ||
+            a.pout || !a.head_w || !a.head_b)
+            return hipErrorInvalidValue;
+        return launch_rows_w<1, MODE_SAME, EPI_HEAD>(a, st);
     }
-    if (a.g.mode == MODE_POOL)
-        hipLaunchKernelGGL((k_conv_tiled<NT, MODE_POOL, E>), grid, dim3(256), 0, st, a, per);
-    else if (a.g.mode == MODE_UP)
-        hipLaunchKernelGGL((k_conv_tiled<NT, MODE_UP, E>), grid, dim3(256), 0, st, a, per);
-    else if (NT == 32 && a.pout)
-        hipLaunchKernelGGL((k_conv_tiled<NT, MODE_SAME, EPI_STAGED>), grid, dim3(256), 0, st, a,
-                           per);
-    else
-        hipLaunchKernelGGL((k_conv_tiled<NT, MODE_SAME, E>), grid, dim3(256), 0, st, a, per);
-    return hipGetLastError();
+    if (a.g.mode == MODE_POOL) return launch_rows_w<NCB, MODE_POOL, EPI_OUT>(a, st);
+    if (a.g.mode == MODE_UP) return launch_rows_w<NCB, MODE_UP, EPI_OUT>(a, st);
+    return launch_rows_w<NCB, MODE_SAME, EPI_OUT>(a, st);
 }
 
 hipError_t conv_stem(const ConvP& a0, const ConvP& a, hipStream_t st) {
@@ -1514,9 +1700,11 @@ hipError_t conv3x3(const ConvP& a, hipStream_t st) {
         hipLaunchKernelGGL(k_conv_first, grid, dim3(256), 0, st, a);
         return hipGetLastError();
     }
-    if (a.g.C % 32 == 0 && a.Cout % 32 == 0)
-        return a.Cout % 64 == 0 ? launch_tiled<64>(a, st) : launch_tiled<32>(a, st);
-    if (a.pout || a.head_out || a.bwd >= 0) return hipErrorInvalidValue;   // only the tiled kernels fuse
+    // (an image of 64 GiB and more is past the row kernel's offsets)
+    if (a.g.C % 32 == 0 && a.Cout % 32 == 0 &&
+        (double)a.g.Hin * a.g.Win * (a.g.cs / 8) < 4294967296.0)
+        return a.Cout % 64 == 0 ? launch_rows<2>(a, st) : launch_rows<1>(a, st);
+    if (a.pout || a.head_out || a.bwd >= 0) return hipErrorInvalidValue;   // only the row kernel fuses
     const int P = a.B * a.H * a.W;
     hipLaunchKernelGGL(k_conv3x3, dim3((P + 255) / 256, (a.Cout + 31) / 32), dim3(256), 0, st, a);
     return hipGetLastError();

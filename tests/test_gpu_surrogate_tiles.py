@@ -13,7 +13,7 @@ from oracle import unet as U
 pytestmark = pytest.mark.gpu
 
 U32 = 2.0 ** -24
-SAME, UP = 0, 1
+SAME, UP, POOL = 0, 1, 2
 
 
 def bf16(a):
@@ -57,3 +57,38 @@ def test_layer_at_tile_edges(size, cin, cout, mode):
     n = B * H * W + 1
     assert np.all(np.abs(dw.cpu().double().numpy() - rdw) <= n * U32 * adw)
     assert np.all(np.abs(db.cpu().double().numpy() - rdb) <= n * U32 * adb)
+
+
+# (batch, channels out): enough tiles for the most rows a wave and several tiles a workgroup,
+# 64 output channels a workgroup and 32
+@pytest.mark.parametrize("mode", [SAME, UP, POOL], ids=["same", "up", "pool"])
+@pytest.mark.parametrize("cin", [32, 64, 96])
+@pytest.mark.parametrize("batch,cout", [(11, 256), (43, 32)])
+def test_layer_of_many_tiles(batch, cout, cin, mode):
+    from paper_1812_00118_amd.surrogate import conv_fwd
+    B, H, W = batch, 30, 66
+    rng = np.random.default_rng(cin + cout + mode)
+    hin, win = {SAME: (H, W), UP: (H // 2, W // 2), POOL: (2 * H, 2 * W)}[mode]
+    x = bf16(rng.integers(-8, 9, (B, hin, win, cin)) / 8)
+    w = bf16(rng.standard_normal((cout, 3, 3, cin)) * np.sqrt(2.0 / (9 * cin)))
+    pre, _ = conv_fwd(dev(x), dev(w), None, mode=mode)
+    torch.cuda.synchronize()
+    # averages of four eighths take five fractional bits and are rounded to BF16 as the input is
+    xin = U.upsample2(x) if mode == UP else bf16(U.avgpool2(x)) if mode == POOL else x
+    for i in range(B):
+        ref = U.conv3x3(xin[i:i + 1], w, np.zeros(cout))
+        err = np.abs(pre[i:i + 1].cpu().double().numpy() - ref)
+        assert np.all(err <= 9 * cin * U32 * U.conv3x3(np.abs(xin[i:i + 1]), np.abs(w), np.zeros(cout)))
+
+
+@pytest.mark.parametrize("row", [4000, 8400, 8970])
+def test_layer_of_an_image_past_4_gib(row):
+    """Rows below and past the fourth GiB equal those of an image of their neighbourhood."""
+    from paper_1812_00118_amd.surrogate import conv_fwd
+    H, W, cin, cout = 9000, 4096, 64, 32
+    g = torch.Generator(device="cuda").manual_seed(row)
+    x = torch.empty((1, H, W, cin), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    w = torch.empty((cout, 3, 3, cin), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    pre, _ = conv_fwd(x, w)
+    near, _ = conv_fwd(x[:, row:row + 18].contiguous(), w)
+    assert torch.equal(pre[:, row + 1:row + 17], near[:, 1:17])
