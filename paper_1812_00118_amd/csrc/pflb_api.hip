@@ -161,19 +161,24 @@ bool inplace(const pflb_params* p) { return p->storage == PFLB_STORE_FP32_INPLAC
 uint32_t sites(const pflb_params* p) { return (uint32_t)p->nx * p->ny * p->nz; }
 
 // Planes per workgroup of the fused step for nctx contexts of one launch.
-// D3Q19: a CU runs its share of the B workgroups, each marching bz planes and
-// re-gathering two more, so the critical path is ceil(B / CUs) (bz + 2) planes; at least
-// two workgroups per CU are needed to hide the gathers' latency.  bz minimises that path
-// among the choices that give two per CU (else the most workgroups).  This reproduces
-// every measured optimum: 128^3 16 planes (8 and 32 slower), 256x256x128 64 (16, 32
-// slower), 256^3 128, and 192^3, where 48 planes (576 workgroups, 2.25 per CU) measured
-// 16% slower than 16.  Where even whole columns give more than two workgroups per CU
+// D3Q19: a CU has room for two workgroups (registers), so the B workgroups run in rounds of
+// two per CU, each round marching bz planes and re-gathering two more; a last round of at
+// most one per CU costs less than a full one, LAST of it: 0.55 in FP32, where two workgroups
+// on a CU share its bandwidth, 0.8 in FP16S (128^3 in 256 workgroups against 512: 0.61 and
+// 0.80 of the time per plane; 0.55 chooses better in FP32).  bz minimises rounds (bz + 2); a
+// domain that cannot give two per CU takes the most workgroups.  The choice is within 0.4% of
+// the best of all chunk counts on average over 17 domains of 60x64x200 to 256x256x128, 3.7%
+// at worst.  Counting one workgroup per CU and asking for two of them, as the rule did
+// before, left rounds half empty: us/step before and after,
+// 537x50x198 FP16S 572 and 437 (FP32 565 and 471), 150x120x100 FP16S 216 and 181, 210x66x90
+// FP16S 136 and 98, 200x90x70 FP32 140 and 118; 128^3 and 256x256x128 keep 16 and 64 planes.
+// Where even whole columns give more than two workgroups per CU
 // (several rounds of workgroups whatever bz), long marches let the running workgroups
 // drift apart in z and touch many more pages at once: there 16 planes, which keeps
-// them within a few planes of each other.  Measured against the model's choice, FP32
+// them within a few planes of each other.  Measured against the longest marches, FP32
 // (FP16S): 1000x1000x268 24% faster, the best of eight plane counts (0.7% slower);
 // 512x512x256 2.6% (5.8%) and 384^3 2% faster (3.6% slower); 512^3 11% (4.4%) faster;
-// 448^3 8% (9%) slower, where the model's 56 planes were the best of four.  On average
+// 448^3 8% (9%) slower, where 56 planes were the best of four.  On average
 // 7% faster in FP32 and neutral in FP16S; no single count is best everywhere.
 // D2Q9 (one-wave workgroups): about 2048 workgroups, at most 4 planes.  Measured: 256x1024
 // Rayleigh-Taylor, 2 planes beat 1, 4 and 8 (1.6x over 8); a lone 256x256 domain runs
@@ -196,28 +201,26 @@ int bz_override() {
     return env && atoi(env) > 0 ? atoi(env) : 0;
 }
 
-int pick_bz(const Geom& G, int lattice, int nctx) {
+int pick_bz(const Geom& G, int lattice, bool half, int nctx) {
     if (const int bz = bz_override()) return bz;
     const long nz = G.nz;
     if (lattice == 19) {
         const long cols = (long)((G.nx + 63) / 64) * ((G.ny + 3) / 4) * nctx;
         const long cus = device_cus();
         if (cols > 2 * cus) return (int)(nz < 16 ? nz : 16);
-        long best = nz, best_cost = -1;
-        bool best_enough = false;
-        long prev_chunks = -1;
-        for (long bz = (nz < 8 ? nz : 8); bz <= nz; ++bz) {
-            const long chunks = (nz + bz - 1) / bz;
-            if (chunks == prev_chunks) continue;           // same split, longer chunks
-            prev_chunks = chunks;
-            const long B = cols * chunks;
-            const bool enough = B >= 2 * cus;
-            const long cost = ((B + cus - 1) / cus) * (bz + 2);
-            if (best_cost < 0 || (enough && !best_enough) ||
-                (enough == best_enough && (enough ? cost < best_cost : false))) {
+        const long least = nz < 8 ? nz : 8;
+        if (cols * ((nz + least - 1) / least) < 2 * cus) return (int)least;
+        const double last = half ? 0.8 : 0.55;
+        long best = nz;
+        double best_cost = -1.0;
+        for (long bz = least; bz <= nz; ++bz) {
+            const long B = cols * ((nz + bz - 1) / bz);
+            const long rem = B % (2 * cus);
+            const double rounds = (double)(B / (2 * cus)) + (rem == 0 ? 0.0 : rem <= cus ? last : 1.0);
+            const double cost = rounds * (double)(bz + 2);
+            if (best_cost < 0.0 || cost < best_cost) {
                 best = bz;
                 best_cost = cost;
-                best_enough = enough;
             }
         }
         return (int)best;
@@ -312,7 +315,7 @@ void derive(pflb_ctx* c) {
     c->L.tile = 0;
     const char* tenv = getenv("PFLB_TILE");
     if (tenv && atoi(tenv) >= 0 && atoi(tenv) <= 3) c->L.tile = atoi(tenv);
-    c->L.bz = pick_bz(G, p.lattice, 1);
+    c->L.bz = pick_bz(G, p.lattice, c->L.half, 1);
     c->L.wide = G.S > (1u << 28) - 64u;
     c->L.fuse = p.lattice == 9 && p.storage == PFLB_STORE_FP32 && !c->L.wide && !G.open &&
                 !m.moving && !m.wetting && !bz_override();
@@ -884,7 +887,7 @@ extern "C" int pflb_step_many(pflb_ctx* const* c, int n, int nsteps, void* strea
         const int nb = ng - k0 < BATCH_MAX ? ng - k0 : BATCH_MAX;
         Launch a = gr[k0]->L;
         a.stream = (hipStream_t)stream;
-        a.bz = pick_bz(a.G, a.q, nb);
+        a.bz = pick_bz(a.G, a.q, a.half, nb);
         a.fuse = a.fuse && !bz_override();
         StepBatch bt;
         memset(&bt, 0, sizeof(bt));
