@@ -177,6 +177,13 @@ std::string check_cfg(const pfsur_cfg* c) {
     return "";
 }
 
+// The gradients' way to the host (send_part)
+struct Readback {
+    hipStream_t st = nullptr;
+    float* host = nullptr;                   // page-locked, PL.total floats
+    hipEvent_t ready[NL + 1] = {}, here[NL + 1] = {};
+};
+
 }  // namespace
 
 struct pfsur_ctx {
@@ -187,6 +194,7 @@ struct pfsur_ctx {
     __bf16* wf[NL] = {};
     __bf16* wt[NL] = {};
     int t = 0;
+    Readback rb;
     std::string err;
 };
 
@@ -288,8 +296,60 @@ int run_forward(pfsur_ctx* c, const void* x, float* out, int B, char* ws, bool t
     return PFLB_OK;
 }
 
-// loss and gradients of all parameters into c->grad, after run_forward(training)
-int run_backward(pfsur_ctx* c, const void* x, const float* y, int B, char* ws, hipStream_t st) {
+// The way of the gradients to the host while the backward pass still runs: each layer's go
+// to page-locked memory on a stream of their own as soon as they are complete, and from
+// there into the caller's array by the host, which has nothing else to do.  (A copy of all
+// of them to pageable memory after the pass took 0.5 ms of the 3.0 ms of a 16x256x256 batch.)
+// Part l < NL is layer l's, part NL the head's.
+size_t part_at(int l) { return l < NL ? PL.w[l] : PL.head; }
+size_t part_size(int l) { return (l + 1 < NL ? PL.w[l + 1] : l < NL ? PL.head : PL.total) - part_at(l); }
+
+void free_readback(Readback& rb) {
+    for (hipEvent_t& e : rb.ready)
+        if (e) (void)hipEventDestroy(e), e = nullptr;
+    for (hipEvent_t& e : rb.here)
+        if (e) (void)hipEventDestroy(e), e = nullptr;
+    if (rb.st) (void)hipStreamDestroy(rb.st);
+    if (rb.host) (void)hipHostFree(rb.host);
+    rb.st = nullptr;
+    rb.host = nullptr;
+}
+
+// the context's own, made by its first use; nullptr where the memory cannot be had
+Readback* readback_of(pfsur_ctx* c) {
+    Readback& rb = c->rb;
+    if (rb.host) return &rb;
+    bool ok = hipStreamCreateWithFlags(&rb.st, hipStreamNonBlocking) == hipSuccess;
+    for (int l = 0; l <= NL && ok; ++l)
+        ok = hipEventCreateWithFlags(&rb.ready[l], hipEventDisableTiming) == hipSuccess &&
+             hipEventCreateWithFlags(&rb.here[l], hipEventDisableTiming) == hipSuccess;
+    void* host = nullptr;
+    if (ok) ok = hipHostMalloc(&host, PL.total * 4, hipHostMallocDefault) == hipSuccess;
+    rb.host = ok ? static_cast<float*>(host) : nullptr;
+    if (!ok) {
+        free_readback(rb);
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    return &rb;
+}
+
+// part l is complete in c->grad once what st holds now has run
+hipError_t send_part(pfsur_ctx* c, Readback* rb, int l, hipStream_t st) {
+    if (!rb) return hipSuccess;
+    hipError_t e = hipEventRecord(rb->ready[l], st);
+    if (e == hipSuccess) e = hipStreamWaitEvent(rb->st, rb->ready[l], 0);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(rb->host + part_at(l), c->grad + part_at(l), part_size(l) * 4,
+                           hipMemcpyDeviceToHost, rb->st);
+    if (e == hipSuccess) e = hipEventRecord(rb->here[l], rb->st);
+    return e;
+}
+
+// loss and gradients of all parameters into c->grad, after run_forward(training), and on
+// their way to rb, if there is one
+int run_backward(pfsur_ctx* c, const void* x, const float* y, int B, char* ws, hipStream_t st,
+                 Readback* rb) {
     const int H = c->cfg.H, W = c->cfg.W;
     const Plan p = make_plan(H, W, B, true);
     const size_t P0 = (size_t)B * H * W;
@@ -306,6 +366,7 @@ int run_backward(pfsur_ctx* c, const void* x, const float* y, int B, char* ws, h
     constexpr size_t nh = PFSUR_OUT_CH * (HEAD_C + 1);
     SUR_TRY(reduce_splits(part, (int)head_blocks(P0), nh, nh, nh, c->grad + PL.head, nullptr, st),
             "head reduce");
+    SUR_TRY(send_part(c, rb, NL, st), "gradient read-back");
     for (int l = NL - 1; l >= 0; --l) {
         const LayerDef& L = LAYERS[l];
         const int Hl = H >> L.level, Wl = W >> L.level;
@@ -318,6 +379,7 @@ int run_backward(pfsur_ctx* c, const void* x, const float* y, int B, char* ws, h
         wg.Cout = L.Cout;
         wg.part = part;
         SUR_TRY(wgrad(wg, c->grad + PL.w[l], c->grad + PL.b[l], st), "wgrad");
+        SUR_TRY(send_part(c, rb, l, st), "gradient read-back");
         if (l == 0) continue;
         // the input gradient, into the dz of the layer before (and the skip connection's half)
         const LayerDef& A = LAYERS[l - 1];
@@ -380,14 +442,19 @@ DensTab dens_tab(const double* rho, int b0, int nb) {
     return d;
 }
 
-// forward + backward; *loss (host) = mean squared error of the forward pass
+// forward + backward; *loss (host) = mean squared error of the forward pass; the gradients
+// also into host_grad, if given, by way of rb
 int forward_backward(pfsur_ctx* c, const void* x, const float* y, int batch, float* loss,
-                     char* ws, hipStream_t st) {
+                     char* ws, hipStream_t st, Readback* rb = nullptr, float* host_grad = nullptr) {
     const Plan p = make_plan(c->cfg.H, c->cfg.W, batch, true);
     int r = run_forward(c, x, nullptr, batch, ws, true, st);
     if (r) return r;
-    r = run_backward(c, x, y, batch, ws, st);
+    r = run_backward(c, x, y, batch, ws, st, rb);
     if (r) return r;
+    for (int l = NL; rb && l >= 0; --l) {
+        SUR_TRY(hipEventSynchronize(rb->here[l]), "gradient read-back");
+        memcpy(host_grad + part_at(l), rb->host + part_at(l), part_size(l) * 4);
+    }
     double sum = 0.0;
     SUR_TRY(hipMemcpyAsync(&sum, ws + p.loss, sizeof(double), hipMemcpyDeviceToHost, st),
             "loss read-back");
@@ -461,6 +528,7 @@ int pfsur_create(const pfsur_cfg* cfg, pfsur_ctx** out) {
 
 void pfsur_destroy(pfsur_ctx* c) {
     if (!c) return;
+    free_readback(c->rb);
     if (c->mem) (void)hipFree(c->mem);
     delete c;
 }
@@ -617,6 +685,16 @@ int pfsur_gradients(pfsur_ctx* c, const void* x, const float* y, int batch, floa
     if (r) return r;
     if (!host_grad) return fail(c, PFLB_ERR_PARAM, "NULL gradient array");
     hipStream_t st = (hipStream_t)stream;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const bool plain = hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+    if (Readback* rb = plain ? readback_of(c) : nullptr) {
+        r = forward_backward(c, x, y, batch, loss, static_cast<char*>(workspace), st, rb, host_grad);
+        // (after an error too, no copy is left in flight)
+        const hipError_t e = hipStreamSynchronize(rb->st);
+        if (r) return r;
+        SUR_TRY(e, "gradient read-back");
+        return PFLB_OK;
+    }
     r = forward_backward(c, x, y, batch, loss, static_cast<char*>(workspace), st);
     if (r) return r;
     SUR_TRY(hipMemcpyAsync(host_grad, c->grad, PL.total * 4, hipMemcpyDeviceToHost, st),
