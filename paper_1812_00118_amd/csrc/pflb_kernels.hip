@@ -5,9 +5,11 @@
 //   k_equilibrium  pre-collision equilibria from (phi, u, P); *_j_b: from (phi, J, P)
 //   k_set_state    pre-collision distributions -> pull storage
 //   k_get_state    pull storage -> pre-collision distributions
-//   k_phi, k_macro read-out of phi, P, J, u (end of Section 2)
+//   k_read, k_phi  read-out of phi, P, J, u (end of Section 2)
 //   *_b            the same over a batch of contexts (blockIdx.y = context)
 //   k_mass_*       deterministic float64 sum of phi and non-finite flag
+#include <algorithm>
+
 #include "pflb_device.hpp"
 #include "pflb_internal.hpp"
 
@@ -627,7 +629,23 @@ __device__ __forceinline__ void phi_site(const Geom& G, const Codec& cd, uint32_
     phi[s] = (float)pull_site_h<L, ST, WALLS>(b, G, make_col(G, x, y), make_zrow(G, z), cd, f);
 }
 
-// P, J and u of site s (each output may be NULL) from the state and the phi field
+// P, J and u of site s (each output may be NULL) from phi around it and its g moments
+template <class L>
+__device__ __forceinline__ void put_macro(const Model& m, uint32_t N, uint32_t s,
+                                          const float (&pn)[L::Q], const GMom& gm,
+                                          float* __restrict__ P, float* __restrict__ J,
+                                          float* __restrict__ U) {
+    const Macro a = macros<L>(m, pn, gm);
+    if (P) P[s] = a.P;
+    const float jv[3] = {a.jx, a.jy, a.jz};
+    const float uv[3] = {a.ux, a.uy, a.uz};
+    for (int c = 0; c < L::D; ++c) {
+        if (J) J[(size_t)c * N + s] = jv[user_axis<L>(c)];
+        if (U) U[(size_t)c * N + s] = uv[user_axis<L>(c)];
+    }
+}
+
+// the same from the state and the phi field
 template <class L, class ST, int WALLS>
 __device__ __forceinline__ void macro_site(const Geom& G, const Model& m, const Codec& cd,
                                            uint32_t N, uint32_t s, const char* __restrict__ b,
@@ -638,14 +656,7 @@ __device__ __forceinline__ void macro_site(const Geom& G, const Model& m, const 
     float pn[L::Q], hv[L::Q], gv[L::Q];
     phi_stencil<L>(G, m, phi, x, y, z, pn);
     pull_site<L, ST, WALLS>(b, G, make_col(G, x, y), make_zrow(G, z), cd, hv, gv);
-    const Macro a = macros<L>(m, pn, g_moments<L>(gv));
-    if (P) P[s] = a.P;
-    const float jv[3] = {a.jx, a.jy, a.jz};
-    const float uv[3] = {a.ux, a.uy, a.uz};
-    for (int c = 0; c < L::D; ++c) {
-        if (J) J[(size_t)c * N + s] = jv[user_axis<L>(c)];
-        if (U) U[(size_t)c * N + s] = uv[user_axis<L>(c)];
-    }
+    put_macro<L>(m, N, s, pn, g_moments<L>(gv), P, J, U);
 }
 
 template <class L, class ST, int WALLS>
@@ -656,14 +667,97 @@ k_phi(Geom G, Codec cd, uint32_t N, const char* __restrict__ b, float* __restric
     phi_site<L, ST, WALLS>(G, cd, s, b, phi);
 }
 
+// phi, P, J and u (the last three may be NULL) in one pass over the state.  A workgroup takes
+// a tile of sites and its one-site ring: phi of both is gathered into LDS, the tile's own
+// sites keep their g moments in registers, and each site's macros follow from the phi around
+// it.  D3Q19: 64x4 columns, marching BZ planes as k_step does (a rolling buffer of 4 planes,
+// one barrier a plane); D2Q9: 32x8 sites at once.  Bound by reading the state: a kernel for
+// phi and one for the rest read every line of it twice (FP32 holds h and g of a population
+// side by side).  That took 152 us on 128^3 in FP32 (FP16S: 120), this one takes 97 (57); on
+// 64^2, where launches count, 9.1 and 4.4.
 template <class L, class ST, int WALLS>
 __global__ void __launch_bounds__(256)
-k_macro(Geom G, Model m, Codec cd, uint32_t N, const char* __restrict__ b,
-        const float* __restrict__ phi, float* __restrict__ P, float* __restrict__ J,
-        float* __restrict__ U) {
-    const uint32_t s = blockIdx.x * 256u + threadIdx.x;
-    if (s >= N) return;
-    macro_site<L, ST, WALLS>(G, m, cd, N, s, b, phi, P, J, U);
+k_read(Geom G, Model m, Codec cd, int BZ, int ntx, int nty, int nblk, uint32_t N,
+       const char* __restrict__ b, float* __restrict__ phi, float* __restrict__ P,
+       float* __restrict__ J, float* __restrict__ U) {
+    constexpr int Q = L::Q;
+    constexpr int TX = L::USES_Y ? 64 : 32, TR = L::USES_Y ? 4 : 8;   // TR along y (D2Q9: z)
+    constexpr int HX = TX + 2, HR = TR + 2, NR = 2 * HX + 2 * TR;
+    __shared__ float sphi[L::USES_Y ? 4 : 1][HR][HX];
+    const int t = xcd_tile(blockIdx.x, nblk);
+    const int bx = t % ntx, by = t / ntx % nty, bzi = t / ntx / nty;
+    const int tid = threadIdx.x, tx = tid % TX, tr = tid / TX;
+    const int x0 = bx * TX, r0 = by * TR, x = x0 + tx, yr = r0 + tr;
+    const bool active = x < G.nx && yr < (L::USES_Y ? G.ny : G.nz);
+    // every thread gathers a ring site, so that its loads are in flight with the own site's
+    const bool has_ring = tid < NR;
+    const int rid = has_ring ? tid : ((tid & ~63) < NR ? (tid & ~63) : NR - 1);
+    int rhx, rhr;
+    if (rid < HX) { rhx = rid; rhr = 0; }
+    else if (rid < 2 * HX) { rhx = rid - HX; rhr = HR - 1; }
+    else if (rid < 2 * HX + TR) { rhx = 0; rhr = 1 + rid - 2 * HX; }
+    else { rhx = HX - 1; rhr = 1 + rid - 2 * HX - TR; }
+    const int rx = x0 - 1 + rhx, rr = r0 - 1 + rhr;
+    auto wet = [&](float v, int vx, int vy, int vz) {
+        return m.wetting ? wet_ghost(G, m, vx, vy, vz, v) : v;
+    };
+    if constexpr (!L::USES_Y) {
+        const Col own = make_col(G, map_coord(x, G.nx, G.wx), 0);
+        const Col ring = make_col(G, map_coord(rx, G.nx, G.wx), 0);
+        const ZRow zo = make_zrow(G, map_coord(yr, G.nz, G.wz));
+        const ZRow zr = make_zrow(G, map_coord(rr, G.nz, G.wz));
+        float h[Q], g[Q], f[Q];
+        const float po = (float)pull_site<L, ST, WALLS>(b, G, own, zo, cd, h, g);
+        const float pr = (float)pull_site_h<L, ST, WALLS>(b, G, ring, zr, cd, f);
+        keep(pr);
+        sphi[0][tr + 1][tx + 1] = wet(po, x, 0, yr);
+        if (has_ring) sphi[0][rhr][rhx] = wet(pr, rx, 0, rr);
+        __syncthreads();
+        if (!active) return;
+        const uint32_t s = own.base + zo.base;
+        float pn[Q];
+        static_for<0, Q>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            pn[i] = sphi[0][tr + 1 + L::cz(i)][tx + 1 + L::cx(i)];
+        });
+        phi[s] = po;
+        put_macro<L>(m, N, s, pn, g_moments<L>(g), P, J, U);
+    } else {
+        const int z0 = bzi * BZ, zend = min(z0 + BZ, G.nz);
+        const Col own = make_col(G, map_coord(x, G.nx, G.wx), map_coord(yr, G.ny, G.wy));
+        const Col ring = make_col(G, map_coord(rx, G.nx, G.wx), map_coord(rr, G.ny, G.wy));
+        // plane z of the tile and its ring into LDS
+        auto plane_in = [&](int z, GMom& gm, float& ph) {
+            const ZRow r = make_zrow(G, map_coord(z, G.nz, G.wz));
+            float h[Q], g[Q], f[Q];
+            ph = (float)pull_site<L, ST, WALLS>(b, G, own, r, cd, h, g);
+            const float pr = (float)pull_site_h<L, ST, WALLS>(b, G, ring, r, cd, f);
+            keep(pr);
+            gm = g_moments<L>(g);
+            sphi[z & 3][tr + 1][tx + 1] = wet(ph, x, yr, z);
+            if (has_ring) sphi[z & 3][rhr][rhx] = wet(pr, rx, rr, z);
+        };
+        GMom gm, gn;
+        float ph, pnext;
+        plane_in(z0 - 1, gm, ph);
+        plane_in(z0, gm, ph);
+        for (int z = z0; z < zend; ++z) {
+            plane_in(z + 1, gn, pnext);
+            lds_barrier();
+            if (active) {
+                const uint32_t s = own.base + (uint32_t)z * G.sxy;
+                float pn[Q];
+                static_for<0, Q>([&](auto I) {
+                    constexpr int i = decltype(I)::value;
+                    pn[i] = sphi[(z + L::cz(i)) & 3][tr + 1 + L::cy(i)][tx + 1 + L::cx(i)];
+                });
+                phi[s] = ph;
+                put_macro<L>(m, N, s, pn, gm, P, J, U);
+            }
+            gm = gn;
+            ph = pnext;
+        }
+    }
 }
 
 template <class L, class ST, int WALLS>
@@ -1179,11 +1273,23 @@ hipError_t launch_get_state(const Launch& a, uint32_t N, const void* b, float* h
 template <class L, class ST, int WALLS>
 static hipError_t read_t(const Launch& a, uint32_t N, const void* b, float* phi, float* P,
                          float* J, float* U) {
-    hipLaunchKernelGGL((k_phi<L, ST, WALLS>), grid1(N), dim3(256), 0, a.stream, a.G, a.cd, N,
-                       static_cast<const char*>(b), phi);
-    if (P || J || U)
-        hipLaunchKernelGGL((k_macro<L, ST, WALLS>), grid1(N), dim3(256), 0, a.stream, a.G, a.m,
-                           a.cd, N, static_cast<const char*>(b), phi, P, J, U);
+    const char* c = static_cast<const char*>(b);
+    if (!P && !J && !U) {
+        hipLaunchKernelGGL((k_phi<L, ST, WALLS>), grid1(N), dim3(256), 0, a.stream, a.G, a.cd, N, c,
+                           phi);
+        return hipGetLastError();
+    }
+    const int ntx = (a.G.nx + (L::USES_Y ? 63 : 31)) / (L::USES_Y ? 64 : 32);
+    const int nty = L::USES_Y ? (a.G.ny + 3) / 4 : (a.G.nz + 7) / 8;
+    // planes a march (two more are gathered for phi alone): as many workgroups as are resident
+    // at once, four per CU, but at least 6 planes.  Measured, us at 4, 8, 16 and 32 planes:
+    // 128^3 FP32 107, 97, 96, 126 (here 8); 256x256x128 474, 416, 384, 376 (32);
+    // 150x60x70 FP16S 34, 33, 45, 82 (6: 34)
+    const int chunks = std::max(1, 1024 / (ntx * nty));
+    const int bz = std::max(6, (a.G.nz + chunks - 1) / chunks);
+    const int nblk = ntx * nty * (L::USES_Y ? (a.G.nz + bz - 1) / bz : 1);
+    hipLaunchKernelGGL((k_read<L, ST, WALLS>), dim3(nblk), dim3(256), 0, a.stream, a.G, a.m, a.cd,
+                       bz, ntx, nty, nblk, N, c, phi, P, J, U);
     return hipGetLastError();
 }
 
