@@ -222,11 +222,9 @@ __device__ __forceinline__ void tile_values(const f32x16 (&acc)[MB][NB], int mb,
                                             const float* sBias, float (&v)[16]) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const float4 b = *reinterpret_cast<const float4*>(&sBias[nb * 32 + 8 * q + 4 * g]);
-        v[4 * q] = acc[mb][nb][4 * q] + b.x;
-        v[4 * q + 1] = acc[mb][nb][4 * q + 1] + b.y;
-        v[4 * q + 2] = acc[mb][nb][4 * q + 2] + b.z;
-        v[4 * q + 3] = acc[mb][nb][4 * q + 3] + b.w;
+        const f32x4 b = *reinterpret_cast<const f32x4*>(&sBias[nb * 32 + 8 * q + 4 * g]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[4 * q + e] = acc[mb][nb][4 * q + e] + b[e];
     }
 }
 
@@ -1109,7 +1107,10 @@ __global__ void __launch_bounds__(256, 2) k_conv_stem(ConvP a0, ConvP a, int til
 // the workgroup's sums go to part[split].  Bound by the matrix cores together with the L2
 // reads (37 KB a patch) and their latency; the form before this one transposed through 176 two-byte LDS
 // writes per thread and patch and ran the layer 64 -> 64 on 16x128x128 in 76 us; this one
-// takes 35 us (0.55 PFLOP/s; 19 GFLOP), of which the matrix cores are busy 9.
+// takes 32 us (0.6 PFLOP/s; 19 GFLOP), of which the matrix cores are busy 9.  Without its
+// products, its loads or its final sums it takes 5 to 8 us less each: they overlap in part
+// only.  (Loads straight into LDS in two stages changed nothing; sums of one tap at a time in
+// place of three cost 2.5 us.)
 // ---------------------------------------------------------------------------
 // Operand of a product over 16 consecutive pixels: lane l gets pixels 8(l/32)..+7 of channel
 // l%32 from pixel-major LDS of 64 bytes a pixel.  A transposing read takes, in each group of
@@ -1130,9 +1131,14 @@ __global__ void __launch_bounds__(256, 2) k_wgrad_tiled(WgradP a, int patches_pe
                                                         int npatch, int nsplit) {
     // the halo of an upsampled input is staged at its own resolution
     constexpr int XE = MODE == MODE_UP ? UPH : HP;
-    __shared__ __align__(16) __bf16 sD[TP * TP * 32];
-    __shared__ __align__(16) __bf16 sX[XE * XE * 32];
-    __shared__ float red[4 * 32 * RED_STRIDE];
+    union Shared {
+        struct {
+            __bf16 d[TP * TP * 32], x[XE * XE * 32];
+        } in;
+        float red[3][4][32][RED_STRIDE];           // of three taps' sums: wave, output, input channel
+    };
+    __shared__ __align__(16) Shared sh;
+    __bf16 *const sD = sh.in.d, *const sX = sh.in.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l32 = lane & 31, g = lane >> 5;
     const int C = a.g.C;
@@ -1149,11 +1155,9 @@ __global__ void __launch_bounds__(256, 2) k_wgrad_tiled(WgradP a, int patches_pe
     const bf16x8 zero8 = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
     const bool with_bias = c0 == 0;
 
-    f32x16 acc[9], accb;
+    f32x16 acc[10];                                // the taps, then the bias
 #pragma unroll
-    for (int j = 0; j < 16; ++j) accb[j] = 0.0f;
-#pragma unroll
-    for (int t = 0; t < 9; ++t)
+    for (int t = 0; t < 10; ++t)
 #pragma unroll
         for (int j = 0; j < 16; ++j) acc[t][j] = 0.0f;
 
@@ -1223,7 +1227,7 @@ __global__ void __launch_bounds__(256, 2) k_wgrad_tiled(WgradP a, int patches_pe
         if (with_bias)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                accb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[r], ones, accb, 0, 0, 0);
+                acc[9] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[r], ones, acc[9], 0, 0, 0);
         // halo rows 4w + i: output row r uses row i = r + dy for tap row dy
 #pragma unroll
         for (int i = 0; i < 6; ++i) {
@@ -1243,32 +1247,40 @@ __global__ void __launch_bounds__(256, 2) k_wgrad_tiled(WgradP a, int patches_pe
             }
         }
     }
-    // fixed-order sum of the 4 waves, one tap (then the bias) at a time: part[split] holds
+    // fixed-order sum of the 4 waves, three taps (then the bias) at a time: part[split] holds
     // [Cout][9][C], then [Cout].  (Barriers that wait for each tap's stores measured
     // 12% slower over the network's layers.)
     float* part = a.part + (size_t)split * ((size_t)a.Cout * 9 * C + a.Cout);
-    auto put = [&](const f32x16& v, auto&& store_at) {
+    auto put = [&](auto first, auto count, auto&& store_at) {
         lds_barrier();
 #pragma unroll
-        for (int j = 0; j < 16; ++j)
-            red[(wave * 32 + 8 * (j >> 2) + 4 * g + (j & 3)) * RED_STRIDE + l32] = v[j];
+        for (int t = 0; t < count; ++t)
+#pragma unroll
+            for (int j = 0; j < 16; ++j)
+                sh.red[t][wave][8 * (j >> 2) + 4 * g + (j & 3)][l32] = acc[first + t][j];
         lds_barrier();
-        for (int k = threadIdx.x; k < 1024; k += 256) {
-            const int o = k >> 5, c = k & 31;
-            const float* r = red + o * RED_STRIDE + c;
-            store_at(o, c, ((r[0] + r[32 * RED_STRIDE]) + r[64 * RED_STRIDE]) + r[96 * RED_STRIDE]);
-        }
+#pragma unroll
+        for (int t = 0; t < count; ++t)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int o = (threadIdx.x >> 5) + 8 * k, c = threadIdx.x & 31;
+                store_at(first + t, o, c,
+                         ((sh.red[t][0][o][c] + sh.red[t][1][o][c]) + sh.red[t][2][o][c]) +
+                             sh.red[t][3][o][c]);
+            }
     };
-#pragma unroll
-    for (int tap = 0; tap < 9; ++tap)
-        put(acc[tap], [&](int o, int c, float v) {
-            if (o0 + o < a.Cout && c0 + c < C)
-                part[((size_t)(o0 + o) * 9 + tap) * C + c0 + c] = v;
-        });
+    auto put_tap = [&](int tap, int o, int c, float v) {
+        if (o0 + o < a.Cout && c0 + c < C) part[((size_t)(o0 + o) * 9 + tap) * C + c0 + c] = v;
+    };
+    static_for<0, 3>([&](auto d) {
+        put(std::integral_constant<int, 3 * decltype(d)::value>{}, std::integral_constant<int, 3>{},
+            put_tap);
+    });
     if (with_bias)
-        put(accb, [&](int o, int c, float v) {
-            if (c == 0 && o0 + o < a.Cout) part[(size_t)a.Cout * 9 * C + o0 + o] = v;
-        });
+        put(std::integral_constant<int, 9>{}, std::integral_constant<int, 1>{},
+            [&](int, int o, int c, float v) {
+                if (c == 0 && o0 + o < a.Cout) part[(size_t)a.Cout * 9 * C + o0 + o] = v;
+            });
 }
 
 // Sum over the splits: sum_s part[s][i], i < n, rows of `stride`, into out[i] for i < nhead
