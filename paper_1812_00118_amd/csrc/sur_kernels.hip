@@ -971,7 +971,9 @@ __global__ void __launch_bounds__(256, 2) k_conv_stem(ConvP a0, ConvP a, int til
     const int l32 = lane & 31, g = lane >> 5;
     const int tx_n = (a.W + TP - 1) / TP, ty_n = (a.H + TP - 1) / TP;
     const int ntile = a.B * tx_n * ty_n;
-    const int t_beg = blockIdx.x * tiles_per_wg;
+    // a contiguous run of tiles per XCD, as k_conv_rows
+    const int xcd = blockIdx.x % 8, xq = gridDim.x / 8, xr = gridDim.x % 8;
+    const int t_beg = (xcd * xq + min(xcd, xr) + (int)blockIdx.x / 8) * tiles_per_wg;
     const int t_end = min(ntile, t_beg + tiles_per_wg);
     const bf16x8 zero8 = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
     auto tile_xy = [&](int t, int& b, int& y0, int& x0) {
