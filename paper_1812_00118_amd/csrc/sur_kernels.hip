@@ -552,13 +552,13 @@ __device__ __forceinline__ void rows_head(const ConvP& a, const f32x16 (&acc)[RW
 //   BWD_POOL  the input was pooled: a quarter of the gradient on each of four pixels at
 //             double resolution, added to the skip connection's in a.fout.
 // (Gradients of 16 samples of 256x256: 725 us of element-wise kernels before, none now.)
-__device__ __forceinline__ void silu_bwd(float (&v)[16], const __bf16* z, int g) {
+__device__ __forceinline__ void load_z(const __bf16* z, int g, bf16x4 (&zq)[4]) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const bf16x4 zq = *reinterpret_cast<const bf16x4*>(z + 8 * q + 4 * g);
+    for (int q = 0; q < 4; ++q) zq[q] = *reinterpret_cast<const bf16x4*>(z + 8 * q + 4 * g);
+}
+__device__ __forceinline__ void silu_bwd(float (&v)[16], const bf16x4 (&zq)[4]) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[4 * q + e] *= silu_grad((float)zq[e]);
-    }
+    for (int e = 0; e < 16; ++e) v[e] *= silu_grad((float)zq[e >> 2][e & 3]);
 }
 
 template <int RW, int BWD>
@@ -578,56 +578,81 @@ __device__ __forceinline__ void rows_bwd(const ConvP& a, const f32x16 (&acc)[RW]
             return;
         }
     }
+    // What a row needs from memory is asked for before the stores of those before it (all of
+    // it at once, or for a pooled input the next pixel's): row by row, each waited for its own
+    // loads and for the stores before them (256x256, 16 images: the first pooling layer's
+    // 105 -> 90 us, the backward layers together 5% less).
+    const int xc = min(t.x, a.W - 1);
+    if constexpr (BWD == BWD_SAME) {
+        bf16x4 z[RW][4];
 #pragma unroll
-    for (int r = 0; r < RW; ++r) {
-        const bool in = t.y + r < a.H && t.x < a.W;
-        float v[16];
-        bf16x4 o[4];
+        for (int r = 0; r < RW; ++r)
+            load_z(a.zin + (((size_t)t.b * a.H + min(t.y + r, a.H - 1)) * a.W + xc) * a.dz_cs + cd, g, z[r]);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) v[e] = acc[r][0][e];
-        if constexpr (BWD == BWD_SAME) {
-            if (in) silu_bwd(v, a.zin + (((size_t)t.b * a.H + t.y + r) * a.W + t.x) * a.dz_cs + cd, g);
+        for (int r = 0; r < RW; ++r) {
+            float v[16];
+            bf16x4 o[4];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) v[e] = acc[r][0][e];
+            silu_bwd(v, z[r]);
             to_bf16(v, 0, o);
             stage_row(so, l32, g, o);
             wave_lds_sync();
             put_row(a, t, r, lane, l32, so, a.dz, a.dz_cs, cd);
             wave_lds_sync();
-        } else if constexpr (BWD == BWD_UP) {
-            if (r & 1) continue;                 // a block's rows are r and r + 1, its lanes l, l^1
+        }
+    } else if constexpr (BWD == BWD_UP) {
+        bf16x4 z[RW / 2 + 1][4];
+        auto half = [&](int r) {
+            return ((size_t)t.b * (a.H >> 1) + (min(t.y + r, a.H - 1) >> 1)) * (a.W >> 1) + (xc >> 1);
+        };
+#pragma unroll
+        for (int r = 0; r < RW; r += 2) load_z(a.zin + half(r) * a.dz_cs + cd, g, z[r / 2]);
+#pragma unroll
+        for (int r = 0; r < RW; r += 2) {        // a block's rows are r and r + 1, its lanes l, l^1
+            float v[16];
+            bf16x4 o[4];
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                const float w = acc[r + (RW > 1)][0][e];
-                v[e] = ((v[e] + __shfl_xor(v[e], 1)) + w) + __shfl_xor(w, 1);
+                const float u = acc[r][0][e], w = acc[r + (RW > 1)][0][e];
+                v[e] = ((u + __shfl_xor(u, 1)) + w) + __shfl_xor(w, 1);
             }
-            if (in && !(t.x & 1)) {
-                const size_t pl = ((size_t)t.b * (a.H >> 1) + ((t.y + r) >> 1)) * (a.W >> 1) + (t.x >> 1);
-                silu_bwd(v, a.zin + pl * a.dz_cs + cd, g);
-                to_bf16(v, 0, o);
+            silu_bwd(v, z[r / 2]);
+            to_bf16(v, 0, o);
+            if (t.y + r < a.H && t.x < a.W && !(t.x & 1)) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    *reinterpret_cast<bf16x4*>(a.dz + pl * a.dz_cs + cd + 8 * q + 4 * g) = o[q];
+                    *reinterpret_cast<bf16x4*>(a.dz + half(r) * a.dz_cs + cd + 8 * q + 4 * g) = o[q];
             }
-        } else {
-            if (!in) continue;
+        }
+    } else {
+        bf16x4 z[2][4];
+        f32x4 f[2][4];
+        auto pixel = [&](int s) {
+            return ((size_t)t.b * 2 * a.H + 2 * min(t.y + (s >> 2), a.H - 1) + (s >> 1 & 1)) * 2 * a.W +
+                   2 * xc + (s & 1);
+        };
+        auto load = [&](int s) {
+            const float* sk = a.fout + pixel(s) * a.f_cs + a.f_c0 + t.cb + 4 * g;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const size_t ph = ((size_t)t.b * 2 * a.H + 2 * (t.y + r) + (k >> 1)) * 2 * a.W +
-                                  2 * t.x + (k & 1);
-                const float* sk = a.fout + ph * a.f_cs + a.f_c0 + t.cb + 4 * g;
-                float u[16];
+            for (int q = 0; q < 4; ++q) f[s & 1][q] = *reinterpret_cast<const f32x4*>(sk + 8 * q);
+            load_z(a.zin + pixel(s) * a.dz_cs + cd, g, z[s & 1]);
+        };
+        load(0);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float4 f = *reinterpret_cast<const float4*>(sk + 8 * q);
-                    u[4 * q] = fmaf(0.25f, v[4 * q], f.x);
-                    u[4 * q + 1] = fmaf(0.25f, v[4 * q + 1], f.y);
-                    u[4 * q + 2] = fmaf(0.25f, v[4 * q + 2], f.z);
-                    u[4 * q + 3] = fmaf(0.25f, v[4 * q + 3], f.w);
-                }
-                silu_bwd(u, a.zin + ph * a.dz_cs + cd, g);
-                to_bf16(u, 0, o);
+        for (int s = 0; s < 4 * RW; ++s) {
+            const int r = s >> 2;
+            if (s + 1 < 4 * RW) load(s + 1);
+            float u[16];
+            bf16x4 o[4];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) u[e] = fmaf(0.25f, acc[r][0][e], f[s & 1][e >> 2][e & 3]);
+            silu_bwd(u, z[s & 1]);
+            to_bf16(u, 0, o);
+            if (t.y + r < a.H && t.x < a.W) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    *reinterpret_cast<bf16x4*>(a.dz + ph * a.dz_cs + cd + 8 * q + 4 * g) = o[q];
+                    *reinterpret_cast<bf16x4*>(a.dz + pixel(s) * a.dz_cs + cd + 8 * q + 4 * g) = o[q];
             }
         }
     }
@@ -1643,7 +1668,8 @@ template <int NCB, int RW, int MODE, int EPI>
 static hipError_t launch_rows_c(const ConvP& a, hipStream_t st) {
     // weights resident for one chunk, or two where the registers allow it
     if (a.g.C == 32) return launch_rows_k<NCB, RW, 1, MODE, EPI>(a, st);
-    if constexpr (RW <= 2 && (RW == 1 || (EPI != EPI_HEAD && EPI != EPI_BWD + BWD_SAME)))
+    if constexpr (RW <= 2 && (RW == 1 || (EPI != EPI_HEAD && EPI != EPI_BWD + BWD_SAME &&
+                                       EPI != EPI_BWD + BWD_POOL)))
         if (a.g.C == 64) return launch_rows_k<NCB, RW, 2, MODE, EPI>(a, st);
     return launch_rows_k<NCB, RW, 0, MODE, EPI>(a, st);
 }
