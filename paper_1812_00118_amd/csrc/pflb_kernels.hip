@@ -5,7 +5,7 @@
 //   k_equilibrium  pre-collision equilibria from (phi, u, P); *_j_b: from (phi, J, P)
 //   k_set_state    pre-collision distributions -> pull storage
 //   k_get_state    pull storage -> pre-collision distributions
-//   k_read, k_phi  read-out of phi, P, J, u (end of Section 2)
+//   k_read         read-out of phi, P, J, u (end of Section 2); k_phi, k_macro: in two passes
 //   *_b            the same over a batch of contexts (blockIdx.y = context)
 //   k_mass_*       deterministic float64 sum of phi and non-finite flag
 #include <algorithm>
@@ -667,6 +667,16 @@ k_phi(Geom G, Codec cd, uint32_t N, const char* __restrict__ b, float* __restric
     phi_site<L, ST, WALLS>(G, cd, s, b, phi);
 }
 
+template <class L, class ST, int WALLS>
+__global__ void __launch_bounds__(256)
+k_macro(Geom G, Model m, Codec cd, uint32_t N, const char* __restrict__ b,
+        const float* __restrict__ phi, float* __restrict__ P, float* __restrict__ J,
+        float* __restrict__ U) {
+    const uint32_t s = blockIdx.x * 256u + threadIdx.x;
+    if (s >= N) return;
+    macro_site<L, ST, WALLS>(G, m, cd, N, s, b, phi, P, J, U);
+}
+
 // phi, P, J and u (the last three may be NULL) in one pass over the state.  A workgroup takes
 // a tile of sites and its one-site ring: phi of both is gathered into LDS, the tile's own
 // sites keep their g moments in registers, and each site's macros follow from the phi around
@@ -1270,13 +1280,23 @@ hipError_t launch_get_state(const Launch& a, uint32_t N, const void* b, float* h
                   : get_state_w<LatD2Q9, StoreF32>(a, N, b, h, g);
 }
 
+// D3Q19 sites from which on k_read is the faster.  Below, the second of two passes finds the
+// state in the caches and k_read's march is a chain of 8 planes and more with few workgroups.
+// Measured after steps, us for two kernels and for k_read: 64^3 with walls all round 17 and 20,
+// 112^3 67 and 68 (FP16S 50 and 51; walls all round 46 and 65, 35 and 49), 128x128x96 90 and 70
+// (68 and 41), 128^3 152 and 97 (120 and 57).
+constexpr uint32_t READ_ONE_PASS = 1550000;
 template <class L, class ST, int WALLS>
 static hipError_t read_t(const Launch& a, uint32_t N, const void* b, float* phi, float* P,
                          float* J, float* U) {
     const char* c = static_cast<const char*>(b);
-    if (!P && !J && !U) {
+    const bool two = L::USES_Y && N < READ_ONE_PASS;
+    if (two || (!P && !J && !U)) {
         hipLaunchKernelGGL((k_phi<L, ST, WALLS>), grid1(N), dim3(256), 0, a.stream, a.G, a.cd, N, c,
                            phi);
+        if (P || J || U)
+            hipLaunchKernelGGL((k_macro<L, ST, WALLS>), grid1(N), dim3(256), 0, a.stream, a.G, a.m,
+                               a.cd, N, c, phi, P, J, U);
         return hipGetLastError();
     }
     const int ntx = (a.G.nx + (L::USES_Y ? 63 : 31)) / (L::USES_Y ? 64 : 32);

@@ -26,6 +26,10 @@ def cases():
         for shape in ((1, 1, 1), (3, 5, 2), (63, 4, 7), (65, 9, 13), (130, 5, 40)):
             yield 19, shape, bc, None
     yield 19, (66, 6, 9), (P_, P_, W_), (0.0, 0.0, 0.0, 0.0, 0.5, -0.3)
+    # past the size from which three-dimensional domains are read in one pass
+    for bc in ((P_, P_, P_), (W_, W_, W_)):
+        yield 19, (131, 106, 113), bc, None
+    yield 19, (131, 106, 113), (P_, P_, W_), (0.0, 0.0, 0.0, 0.0, 0.5, -0.3)
 
 
 @pytest.mark.parametrize("storage", ["fp32", "fp16s"])
